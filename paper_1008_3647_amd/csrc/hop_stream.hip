@@ -45,18 +45,22 @@ namespace ufg {
 namespace {
 using namespace splitk;
 
-// LDS slot of element (row, col) of a slice stored as NX*NX rows of NX:
-// power-of-two NX uses an XOR swizzle (no padding), else one pad column.
+// LDS slot of element (row, col) of a slice stored as NX*NX rows of NX + 1: the
+// pad column spreads the banks for all three line directions (Nx = 8, 16: no
+// conflicts at 8 or 16 bytes an element), and every slot of a line is one base
+// plus an immediate. The XOR swizzle used for Nx = 8, 16 before needed one
+// address register for each of the 2 Nx slots of the y and x lines (plain
+// complex64 Nx = 16 operator: 116 VGPRs for M and 137 for M^T, 87 and 112 now),
+// and the z-planes of a wave shared banks: complex128 M^T at 16^3 x 800, 8 rhs
+// 179.6 -> 176.1 us, complex64 M at 16^3 x 400 43.0 -> 42.5 us, order-2
+// weak-coupling application complex64 372 -> 361 us.
 template <int NX>
 __device__ __forceinline__ int lds_at(int row, int col) {
-  if constexpr ((NX & (NX - 1)) == 0)
-    return row * NX + (col ^ (row & (NX - 1)));
-  else
-    return row * (NX + 1) + col;
+  return row * (NX + 1) + col;
 }
 template <int NX>
 constexpr int lds_slice_elems() {
-  return ((NX & (NX - 1)) == 0) ? NX * NX * NX : NX * NX * (NX + 1);
+  return NX * NX * (NX + 1);
 }
 
 // T^3 of the slice held as z-lines in v (thread (y, x)); result left in v.

@@ -123,7 +123,7 @@ static void transfer_eigenbasis(int nx, double tau, int dispersion, double* U, d
 }
 
 static int alloc_fields(Lattice& L) {
-  const size_t N = (size_t)L.N, V = (size_t)L.V, m = (size_t)L.nx * L.nx;
+  const size_t N = (size_t)L.N;
   double** d[] = {&L.f64.b, &L.f64.sn, &L.f64.cs, &L.f64.scaD, &L.f64.scaL};
   float** f[] = {&L.f32.b, &L.f32.sn, &L.f32.cs, &L.f32.scaD, &L.f32.scaL};
   for (auto pp : d)
@@ -131,30 +131,44 @@ static int alloc_fields(Lattice& L) {
   for (auto pp : f)
     if (hipMalloc(pp, N * sizeof(float)) != hipSuccess) return UFG_ENOMEM;
   if (hipMalloc(&L.sigma, N * sizeof(double)) != hipSuccess) return UFG_ENOMEM;
-  double** dm[] = {&L.f64.T, &L.f64.U, &L.f64.Ut};
-  float** fm[] = {&L.f32.T, &L.f32.U, &L.f32.Ut};
-  for (auto pp : dm)
-    if (hipMalloc(pp, m * sizeof(double)) != hipSuccess) return UFG_ENOMEM;
-  for (auto pp : fm)
-    if (hipMalloc(pp, m * sizeof(float)) != hipSuccess) return UFG_ENOMEM;
-  if (hipMalloc(&L.f64.lam, V * sizeof(double)) != hipSuccess) return UFG_ENOMEM;
-  if (hipMalloc(&L.f32.lam, V * sizeof(float)) != hipSuccess) return UFG_ENOMEM;
   return UFG_OK;
 }
 
 static void free_fields(Lattice& L) {
   void* ptrs[] = {L.f64.b, L.f64.sn, L.f64.cs, L.f64.scaD, L.f64.scaL, L.f32.b, L.f32.sn,
-                  L.f32.cs, L.f32.scaD, L.f32.scaL, L.sigma, L.f64.T, L.f64.U, L.f64.Ut,
-                  L.f32.T, L.f32.U, L.f32.Ut, L.f64.lam, L.f32.lam};
+                  L.f32.cs, L.f32.scaD, L.f32.scaL, L.sigma, L.f64.T, L.f32.T};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
 }
 
-template <typename T>
-static int upload(hipStream_t s, T* dst, const std::vector<double>& src) {
-  std::vector<T> h(src.begin(), src.end());
-  UFG_HIP(hipMemcpyAsync(dst, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice, s));
-  UFG_HIP(hipStreamSynchronize(s));
+// The constants of one precision (T, U, U^T, mode eigenvalues, block forms of U^T
+// and U where they exist) in one allocation, owned through F.T, and one copy.
+template <typename R>
+static int upload_constants(Lattice& L, Fields<R>& F, const std::vector<double>& Ut,
+                            const std::vector<double>& lam) {
+  std::vector<R> h;
+  auto put = [&](const std::vector<double>& v) {
+    const size_t at = h.size();
+    h.insert(h.end(), v.begin(), v.end());
+    h.resize((h.size() + 15) / 16 * 16);  // every part 64-byte aligned or better
+    return at;
+  };
+  std::vector<double> modes = L.mode_fwd_host;
+  modes.insert(modes.end(), L.mode_bwd_host.begin(), L.mode_bwd_host.end());
+  const size_t t = put(L.T_host), u = put(L.U_host), ut = put(Ut), la = put(lam), mo = put(modes);
+  R* base = nullptr;
+  if (hipMalloc(&base, h.size() * sizeof(R)) != hipSuccess) {
+    (void)hipGetLastError();
+    set_error("create_lattice: device allocation failed");
+    return UFG_ENOMEM;
+  }
+  F.T = base + t;
+  F.U = base + u;
+  F.Ut = base + ut;
+  F.lam = base + la;
+  F.modes = modes.empty() ? nullptr : base + mo;
+  UFG_HIP(hipMemcpyAsync(base, h.data(), h.size() * sizeof(R), hipMemcpyHostToDevice, L.stream));
+  UFG_HIP(hipStreamSynchronize(L.stream));
   return UFG_OK;
 }
 
@@ -299,15 +313,8 @@ int create_lattice_dim(int nx, int ntau, int dim, double tau, double g, int dtyp
     for (int k = 0, rest = i; k < dim; ++k, rest /= nx) v *= lam1m[rest % nx];
     lam3[i] = v;
   }
-  int rc = UFG_OK;
-  if (!rc) rc = upload<double>(L->stream, L->f64.T, L->T_host);
-  if (!rc) rc = upload<float>(L->stream, L->f32.T, L->T_host);
-  if (!rc) rc = upload<double>(L->stream, L->f64.U, L->U_host);
-  if (!rc) rc = upload<float>(L->stream, L->f32.U, L->U_host);
-  if (!rc) rc = upload<double>(L->stream, L->f64.Ut, Ut);
-  if (!rc) rc = upload<float>(L->stream, L->f32.Ut, Ut);
-  if (!rc) rc = upload<double>(L->stream, L->f64.lam, lam3);
-  if (!rc) rc = upload<float>(L->stream, L->f32.lam, lam3);
+  int rc = upload_constants<double>(*L, L->f64, Ut, lam3);
+  if (!rc) rc = upload_constants<float>(*L, L->f32, Ut, lam3);
   if (!rc && hipMemsetAsync(L->sigma, 0, sizeof(double) * L->N, L->stream) != hipSuccess)
     rc = UFG_EHIP;
   if (!rc) rc = install_field(*L);

@@ -39,89 +39,11 @@
 #include "hop_stream.h"
 #include "krylov.h"
 #include "krylov_fin.h"
-#include "split_line.h"
+#include "slice_t3.h"
 
 namespace ufg {
 namespace {
 using namespace splitk;
-
-// LDS slot of element (row, col) of a slice stored as NX*NX rows of NX + 1: the
-// pad column spreads the banks for all three line directions (Nx = 8, 16: no
-// conflicts at 8 or 16 bytes an element), and every slot of a line is one base
-// plus an immediate. The XOR swizzle used for Nx = 8, 16 before needed one
-// address register for each of the 2 Nx slots of the y and x lines (plain
-// complex64 Nx = 16 operator: 116 VGPRs for M and 137 for M^T, 87 and 112 now),
-// and the z-planes of a wave shared banks: complex128 M^T at 16^3 x 800, 8 rhs
-// 179.6 -> 176.1 us, complex64 M at 16^3 x 400 43.0 -> 42.5 us, order-2
-// weak-coupling application complex64 372 -> 361 us.
-template <int NX>
-__device__ __forceinline__ int lds_at(int row, int col) {
-  return row * (NX + 1) + col;
-}
-template <int NX>
-constexpr int lds_slice_elems() {
-  return NX * NX * (NX + 1);
-}
-
-// T^3 of the slice held as z-lines in v (thread (y, x)); result left in v.
-// Barriers: stage 1 (thread (y, x) writes its z-line) feeds the y-lines of
-// other waves, and the x-lines feed the z-lines of other waves. The y-lines
-// (z, x) and x-lines (z, y) of one z-plane belong to the same NX consecutive
-// threads, which sit in one wave when NX divides 64: there a wave-level
-// ordering point replaces the block barrier. Each thread's last read and its
-// next first write touch only its own z-line, so no barrier guards the reuse
-// of the buffer by the next slice.
-// MODE 0: T (positions -> positions); 1: U^T (positions -> block-ordered
-// modes); 2: U (modes -> positions). The same three passes serve all three.
-template <int MODE, typename R, int NX>
-__device__ __forceinline__ void line_op(const SplitCoef<R, NX>& c, C2<R> (&v)[NX]) {
-  if constexpr (MODE == 0)
-    split_line<R, NX>(c, v);
-  else if constexpr (MODE == 1)
-    modes_fwd<R, NX>(c, v);
-  else
-    modes_bwd<R, NX>(c, v);
-}
-
-template <typename R, int NX, int MODE = 0, bool KEEP = false>
-__device__ __forceinline__ void slice_T3(const SplitCoef<R, NX>& c, C2<R>* lds, int l,
-                                         C2<R> (&v)[NX]) {
-  const int y = l / NX, x = l - (l / NX) * NX;
-  line_op<MODE, R, NX>(c, v);  // along z
-#pragma unroll
-  for (int z = 0; z < NX; ++z) lds[lds_at<NX>(z * NX + y, x)] = v[z];
-  __syncthreads();
-  C2<R> w[NX];
-  {
-    const int z = l / NX, xx = l - (l / NX) * NX;
-#pragma unroll
-    for (int yy = 0; yy < NX; ++yy) w[yy] = lds[lds_at<NX>(z * NX + yy, xx)];
-    line_op<MODE, R, NX>(c, w);  // along y
-#pragma unroll
-    for (int yy = 0; yy < NX; ++yy) lds[lds_at<NX>(z * NX + yy, xx)] = w[yy];
-  }
-  if constexpr (64 % NX == 0) {
-    // LDS operations of one wave are performed in order; the fences keep the
-    // compiler from moving the reads above the writes
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  } else {
-    __syncthreads();
-  }
-  {
-    const int z = l / NX, yy = l - (l / NX) * NX;
-#pragma unroll
-    for (int xx = 0; xx < NX; ++xx) w[xx] = lds[lds_at<NX>(z * NX + yy, xx)];
-    line_op<MODE, R, NX>(c, w);  // along x
-#pragma unroll
-    for (int xx = 0; xx < NX; ++xx) lds[lds_at<NX>(z * NX + yy, xx)] = w[xx];
-  }
-  __syncthreads();
-  if (KEEP) return;  // the result stays in LDS: z-line of thread (y, x) at lds_at(z NX + y, x)
-#pragma unroll
-  for (int z = 0; z < NX; ++z) v[z] = lds[lds_at<NX>(z * NX + y, x)];
-}
 
 // The y and x stages of T^3 as 16x16x4 FP32 MFMA contractions (Nx = 16,
 // complex64; lattice_tune_transform route 1). A wave owns z-planes 4w..4w+3,
@@ -308,83 +230,6 @@ __device__ __forceinline__ void slice_T3_fft16(const float (&lam)[16], float2* l
   __syncthreads();
 }
 
-// Per-rhs scalars of the fused BiCGStab sources.
-template <typename R>
-struct SrcScal {
-  R br, bi, wr, wi, ar, ai;
-};
-
-template <typename R, int SRC>
-__device__ __forceinline__ SrcScal<R> src_scalars(const HopArgs<R>& a, int r) {
-  SrcScal<R> q{};
-  if (SRC == 0) return q;
-  const RhsState s = reinterpret_cast<const RhsState*>(a.st)[r];
-  if (SRC == 1) {
-    q.br = R(s.beta.x);  // beta = (rho / rho_old)(alpha / omega), set by the finalize
-    q.bi = R(s.beta.y);
-    q.wr = R(s.omega.x);
-    q.wi = R(s.omega.y);
-  } else {
-    q.ar = R(s.alpha.x);
-    q.ai = R(s.alpha.y);
-  }
-  return q;
-}
-
-// Raw buffer access: one 128-bit resource per array (base = the rhs block),
-// a 32-bit lane offset in a VGPR and the slice / z offset in an SGPR.
-// Out-of-range accesses are dropped by the hardware (loads return 0).
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-constexpr int kRsrcWord3 = 0x00020000;  // gfx9 raw buffer, 32-bit data format
-constexpr int kAuxNT = 2;               // non-temporal
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, unsigned bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, kRsrcWord3);
-}
-
-template <typename R, int AUX = 0>
-__device__ __forceinline__ C2<R> bload(__amdgpu_buffer_rsrc_t rs, int vo, int so) {
-  if constexpr (sizeof(R) == 4) {
-    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, vo, so, AUX);
-    return __builtin_bit_cast(C2<R>, v);
-  } else {
-    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, vo, so, AUX);
-    return __builtin_bit_cast(C2<R>, v);
-  }
-}
-
-// Store of one element at byte offset so + vo from base (rsrc describes the
-// same block). 16-byte elements go through a FLAT store: the compiler's
-// wait-state handling for a VALU overwrite of store-data registers does not
-// cover buffer stores with an SGPR offset, and 128-bit buffer stores were
-// seen to write registers already overwritten by the next instruction.
-template <typename R, bool NT>
-__device__ __forceinline__ void bstore(C2<R> v, C2<R>* base, __amdgpu_buffer_rsrc_t rs, int vo,
-                                       int so) {
-  if constexpr (sizeof(R) == 4) {
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rs, vo, so,
-                                          NT ? kAuxNT : 0);
-  } else {
-    C2<R>* p = reinterpret_cast<C2<R>*>(reinterpret_cast<char*>(base) + so + vo);
-    if (NT) {
-      __builtin_nontemporal_store(v.x, &p->x);
-      __builtin_nontemporal_store(v.y, &p->y);
-    } else {
-      *p = v;
-    }
-  }
-}
-
-template <typename R>
-__device__ __forceinline__ R bload_real(__amdgpu_buffer_rsrc_t rs, int vo, int so) {
-  if constexpr (sizeof(R) == 4) {
-    return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b32(rs, vo, so, 0));
-  } else {
-    return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b64(rs, vo, so, 0));
-  }
-}
-
 struct Rsrc {
   __amdgpu_buffer_rsrc_t src, fr, fp, fv, fpnew, dst, aux, rw, pre, post;
 };
@@ -463,32 +308,6 @@ __device__ __forceinline__ bool stream_item(int nslab, int nrhs, int xg, int ri,
   return true;
 }
 
-// Where the transform reads the blocks of T (or U) from. The Nx = 16 blocks
-// are 66 numbers. In FP64 (132 SGPRs) they exceed the scalar register file and
-// the compiler spills them to VGPR lanes (a v_readlane before each use); with
-// IN_LDS the workgroup copies them into LDS once and the transform reads them
-// from there (broadcast reads). Measured per kernel: the fused FP64 M-type
-// operator (t = A s: 227 -> 206 us), the FP64 basis changes and both
-// precisions of basis_pair_kernel (two sets) gain; the plain FP64 operator (103
-// -> 122 us), the M^T-type fused ones and every complex64 operator keep the
-// kernel-argument copy.
-template <bool IN_LDS, typename R, int NX>
-using CoefSlot = typename std::conditional<IN_LDS, SplitCoef<R, NX>, char>::type;
-
-template <bool IN_LDS, typename R, int NX>
-__device__ __forceinline__ const SplitCoef<R, NX>* coef_copy(const SplitCoef<R, NX>& c,
-                                                            CoefSlot<IN_LDS, R, NX>* lds_slot) {
-  if constexpr (IN_LDS) {
-    constexpr int NC = sizeof(SplitCoef<R, NX>) / sizeof(R);
-    for (int i = threadIdx.x; i < NC; i += blockDim.x)
-      reinterpret_cast<R*>(lds_slot)[i] = reinterpret_cast<const R*>(&c)[i];
-    __syncthreads();
-    return lds_slot;
-  } else {
-    return &c;
-  }
-}
-
 __device__ __forceinline__ double wsum(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
@@ -560,7 +379,7 @@ __global__ void __launch_bounds__(NX * NX)
   b.pre = make_rsrc(a.pre, fbytes);
   b.post = make_rsrc(a.post, fbytes);
   const int vo = l * ES, fo = l * FS;
-  SrcScal<R> q = src_scalars<R, SRC>(a, r);
+  SrcScal<R> q = src_scalars<R, SRC>(a.st, r);
   if constexpr (SRC == 2 && RED == 4) {
     if (a.fin_part) {  // the alpha step of the rhs state, see HopArgs
       // thread 0 fetches the state and flags while every thread sums partials
@@ -883,241 +702,6 @@ int launch_nx(const Lattice& L, const HopArgs<R>& a) {
   return launch_dir<R, NX, +1>(L, a, c);
 }
 
-// Basis change of whole slices (no time shift): y = post . M^3 (pre . x),
-// M = U^T (forward: positions -> block-ordered modes) or U (backward), then
-// GENERAL: y = alpha y + beta aux. A workgroup walks a slab of slices of one
-// right-hand side (XCD-aware numbering as above); the slices are independent.
-// SRC 1 / 2: x is built while loading as the BiCGStab p = r + beta (p - omega v)
-// or s = r - alpha v of the rhs state and stored to fpnew (the first basis
-// change of a weak-coupling application takes over the vector update).
-template <typename R, int NX, bool FWD, bool GENERAL, int SRC>
-__global__ void __launch_bounds__(NX * NX)
-    basis_kernel(HopArgs<R> a, SplitCoef<R, NX> c, int ntau, int nslab, int xg, int ri) {
-  constexpr int P = NX * NX, V = NX * NX * NX;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  C2<R>* lds = reinterpret_cast<C2<R>*>(smem_raw);
-  int r, sb;
-  if (!stream_item(nslab, a.nrhs, xg, ri, r, sb)) return;
-  if (a.gate && a.gate[r] == 0) return;
-  constexpr bool kCoefLds = sizeof(R) == 8;
-  __shared__ CoefSlot<kCoefLds, R, NX> coef_lds[1];
-  const SplitCoef<R, NX>& cc = *coef_copy<kCoefLds, R, NX>(c, coef_lds);
-  const int l = threadIdx.x;
-  const int t0 = (int)((long long)sb * ntau / nslab);
-  const int t1 = (int)((long long)(sb + 1) * ntau / nslab);
-  const long long rbase = (long long)r * ntau * V;
-  const SrcScal<R> q = src_scalars<R, SRC>(a, r);
-  for (int t = t0; t < t1; ++t) {
-    const long long o = rbase + (long long)t * V + l;
-    const long long fo = (long long)t * V + l;
-    C2<R> X[NX];
-    if constexpr (SRC == 0) {
-#pragma unroll
-      for (int z = 0; z < NX; ++z) X[z] = a.src[o + z * P];
-    } else {
-#pragma unroll
-      for (int z = 0; z < NX; ++z) {
-        const long long i = o + z * P;
-        const C2<R> rv = a.fr[i], vv = a.fv[i];
-        if constexpr (SRC == 1) {
-          const C2<R> pv = a.fp[i];
-          const R dx = pv.x - (q.wr * vv.x - q.wi * vv.y);
-          const R dy = pv.y - (q.wr * vv.y + q.wi * vv.x);
-          X[z] = C2<R>{rv.x + q.br * dx - q.bi * dy, rv.y + q.br * dy + q.bi * dx};
-        } else {
-          X[z] = C2<R>{rv.x - (q.ar * vv.x - q.ai * vv.y), rv.y - (q.ar * vv.y + q.ai * vv.x)};
-        }
-        a.fpnew[i] = X[z];
-      }
-    }
-    if (a.pre) {
-#pragma unroll
-      for (int z = 0; z < NX; ++z) {
-        const R fz = a.pre[fo + z * P];
-        X[z].x *= fz;
-        X[z].y *= fz;
-      }
-    }
-    R F[NX];
-    C2<R> U[GENERAL ? NX : 1];
-#pragma unroll
-    for (int z = 0; z < NX; ++z) F[z] = a.post ? a.post[fo + z * P] : R(1);
-    if (GENERAL && a.aux) {
-#pragma unroll
-      for (int z = 0; z < NX; ++z) U[GENERAL ? z : 0] = a.aux[o + z * P];
-    }
-    slice_T3<R, NX, FWD ? 1 : 2>(cc, lds, l, X);
-#pragma unroll
-    for (int z = 0; z < NX; ++z) {
-      C2<R> out;
-      out.x = F[z] * X[z].x;
-      out.y = F[z] * X[z].y;
-      if (GENERAL) {
-        const R ar = R(a.alpha.x), ai = R(a.alpha.y);
-        const C2<R> b = out;
-        out.x = ar * b.x - ai * b.y;
-        out.y = ar * b.y + ai * b.x;
-        if (a.aux) {
-          const C2<R> u = U[GENERAL ? z : 0];
-          const R br = R(a.beta.x), bi = R(a.beta.y);
-          out.x += br * u.x - bi * u.y;
-          out.y += br * u.y + bi * u.x;
-        }
-      }
-      a.dst[o + z * P] = out;
-    }
-  }
-}
-
-// Two basis changes of each slice in one pass (the weak-coupling series, whose
-// consecutive orders meet as U^3 then U^3T with only per-site factors between):
-//   z = alpha post . U^3 x + beta aux  (stored to zout when given),
-//   y = U^3T (mid . z).
-// The second transform's first LDS write touches only the thread's own z-line,
-// which the first transform's last read has already consumed.
-template <typename R>
-struct PairArgs {
-  const C2<R>* src = nullptr;
-  C2<R>* dst = nullptr;
-  C2<R>* zout = nullptr;
-  const R* post = nullptr;
-  const R* mid = nullptr;
-  const C2<R>* aux = nullptr;
-  double2 alpha = {1.0, 0.0};
-  double2 beta = {0.0, 0.0};
-  const int* gate = nullptr;
-  int nrhs = 1;
-};
-
-template <typename R, int NX>
-__global__ void __launch_bounds__(NX * NX)
-    basis_pair_kernel(PairArgs<R> a, SplitCoef<R, NX> cb, SplitCoef<R, NX> cf, int ntau,
-                      int nslab, int xg, int ri) {
-  constexpr int P = NX * NX, V = NX * NX * NX;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  C2<R>* lds = reinterpret_cast<C2<R>*>(smem_raw);
-  int r, sb;
-  if (!stream_item(nslab, a.nrhs, xg, ri, r, sb)) return;
-  if (a.gate && a.gate[r] == 0) return;
-  __shared__ SplitCoef<R, NX> coef_lds[2];
-  const SplitCoef<R, NX>& ccb = *coef_copy<true, R, NX>(cb, coef_lds);
-  const SplitCoef<R, NX>& ccf = *coef_copy<true, R, NX>(cf, coef_lds + 1);
-  const int l = threadIdx.x;
-  const int t0 = (int)((long long)sb * ntau / nslab);
-  const int t1 = (int)((long long)(sb + 1) * ntau / nslab);
-  const long long rbase = (long long)r * ntau * V;
-  const R ar = R(a.alpha.x), ai = R(a.alpha.y), br = R(a.beta.x), bi = R(a.beta.y);
-  for (int t = t0; t < t1; ++t) {
-    const long long o = rbase + (long long)t * V + l;
-    const long long fo = (long long)t * V + l;
-    C2<R> X[NX];
-#pragma unroll
-    for (int z = 0; z < NX; ++z) X[z] = a.src[o + z * P];
-    R F[NX], G[NX];
-#pragma unroll
-    for (int z = 0; z < NX; ++z) {
-      F[z] = a.post ? a.post[fo + z * P] : R(1);
-      G[z] = a.mid ? a.mid[fo + z * P] : R(1);
-    }
-    C2<R> Au[NX];
-    if (a.aux) {
-#pragma unroll
-      for (int z = 0; z < NX; ++z) Au[z] = a.aux[o + z * P];
-    }
-    slice_T3<R, NX, 2>(ccb, lds, l, X);  // U^3
-#pragma unroll
-    for (int z = 0; z < NX; ++z) {
-      const C2<R> b = C2<R>{F[z] * X[z].x, F[z] * X[z].y};
-      C2<R> w = C2<R>{ar * b.x - ai * b.y, ar * b.y + ai * b.x};
-      if (a.aux) {
-        w.x += br * Au[z].x - bi * Au[z].y;
-        w.y += br * Au[z].y + bi * Au[z].x;
-      }
-      if (a.zout) {
-        __builtin_nontemporal_store(w.x, &a.zout[o + z * P].x);
-        __builtin_nontemporal_store(w.y, &a.zout[o + z * P].y);
-      }
-      X[z] = C2<R>{G[z] * w.x, G[z] * w.y};
-    }
-    slice_T3<R, NX, 1>(ccf, lds, l, X);  // U^3T
-#pragma unroll
-    for (int z = 0; z < NX; ++z) {
-      a.dst[o + z * P] = X[z];
-    }
-  }
-}
-
-template <typename R, int NX>
-int launch_basis_pair_nx(const Lattice& L, const PairArgs<R>& a) {
-  SplitCoef<R, NX> cb, cf;
-  int k = 0;
-  for (auto& v : cb.es) v = R(L.mode_bwd_host[k++]);
-  for (auto& v : cb.ea) v = R(L.mode_bwd_host[k++]);
-  for (auto& v : cb.os) v = R(L.mode_bwd_host[k++]);
-  for (auto& v : cb.oa) v = R(L.mode_bwd_host[k++]);
-  k = 0;
-  for (auto& v : cf.es) v = R(L.mode_fwd_host[k++]);
-  for (auto& v : cf.ea) v = R(L.mode_fwd_host[k++]);
-  for (auto& v : cf.os) v = R(L.mode_fwd_host[k++]);
-  for (auto& v : cf.oa) v = R(L.mode_fwd_host[k++]);
-  const int nslab = stream_nslab(L);
-  const size_t lds = size_t(lds_slice_elems<NX>()) * sizeof(C2<R>);
-  static bool attr = false;
-  if (!attr) {
-    UFG_HIP(hipFuncSetAttribute((const void*)basis_pair_kernel<R, NX>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    attr = true;
-  }
-  hipLaunchKernelGGL((basis_pair_kernel<R, NX>), dim3(stream_grid(L, a.nrhs)), dim3(NX * NX),
-                     lds, L.stream, a, cb, cf, L.ntau, nslab, stream_group(L),
-                     stream_inner(L));
-  UFG_HIP(hipGetLastError());
-  return UFG_OK;
-}
-
-template <typename R, int NX, bool FWD, bool GENERAL, int SRC = 0>
-int launch_basis_one(const Lattice& L, const HopArgs<R>& a, const SplitCoef<R, NX>& c,
-                     dim3 grid, size_t lds, int nslab) {
-  static bool attr = false;
-  if (!attr) {
-    UFG_HIP(hipFuncSetAttribute((const void*)basis_kernel<R, NX, FWD, GENERAL, SRC>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    attr = true;
-  }
-  hipLaunchKernelGGL((basis_kernel<R, NX, FWD, GENERAL, SRC>), grid, dim3(NX * NX), lds,
-                     L.stream, a, c, L.ntau, nslab, stream_group(L), stream_inner(L));
-  UFG_HIP(hipGetLastError());
-  return UFG_OK;
-}
-
-template <typename R, int NX>
-int launch_basis_nx(const Lattice& L, const HopArgs<R>& a, bool forward) {
-  SplitCoef<R, NX> c;
-  const std::vector<double>& h = forward ? L.mode_fwd_host : L.mode_bwd_host;
-  int k = 0;
-  for (auto& v : c.es) v = R(h[k++]);
-  for (auto& v : c.ea) v = R(h[k++]);
-  for (auto& v : c.os) v = R(h[k++]);
-  for (auto& v : c.oa) v = R(h[k++]);
-  const int nslab = stream_nslab(L);
-  const size_t lds = size_t(lds_slice_elems<NX>()) * sizeof(C2<R>);
-  const dim3 grid(stream_grid(L, a.nrhs));
-  const bool general = (a.alpha.x != 1.0 || a.alpha.y != 0.0 || a.aux != nullptr);
-  if (forward && a.src_mode == 1 && !general)
-    return launch_basis_one<R, NX, true, false, 1>(L, a, c, grid, lds, nslab);
-  if (forward && a.src_mode == 2 && !general)
-    return launch_basis_one<R, NX, true, false, 2>(L, a, c, grid, lds, nslab);
-  if (a.src_mode != 0) {
-    set_error("basis change: a fused source needs the plain forward change");
-    return UFG_EINVAL;
-  }
-  if (forward)
-    return general ? launch_basis_one<R, NX, true, true>(L, a, c, grid, lds, nslab)
-                   : launch_basis_one<R, NX, true, false>(L, a, c, grid, lds, nslab);
-  return general ? launch_basis_one<R, NX, false, true>(L, a, c, grid, lds, nslab)
-                 : launch_basis_one<R, NX, false, false>(L, a, c, grid, lds, nslab);
-}
-
 }  // namespace
 
 int stream_slab(const Lattice& L) {
@@ -1203,66 +787,6 @@ int launch_hop_stream(const Lattice& L, const HopArgs<R>& args) {
   }
 }
 
-template <typename R>
-int launch_basis_stream(const Lattice& L, const HopArgs<R>& args, bool forward) {
-  HopArgs<R> a = args;
-  if (a.beta.x == 0.0 && a.beta.y == 0.0) a.aux = nullptr;
-  if (a.shift != 0 || a.red_mode != 0 || a.id != nullptr) {
-    set_error("basis change: no shift, identity term or reduction");
-    return UFG_EINVAL;
-  }
-  if (a.src_mode != 0 && (a.src_mode > 2 || !a.fr || !a.fv || !a.fpnew || !a.st ||
-                          (a.src_mode == 1 && !a.fp))) {
-    set_error("basis change: incomplete fused source");
-    return UFG_EINVAL;
-  }
-  switch (L.nx) {
-    case 8: return launch_basis_nx<R, 8>(L, a, forward);
-    case 12: return launch_basis_nx<R, 12>(L, a, forward);
-    case 16: return launch_basis_nx<R, 16>(L, a, forward);
-    default: set_error("basis change: unsupported nx"); return UFG_EINVAL;
-  }
-}
-
-template <typename R>
-int launch_basis_pair(const Lattice& L, const C2<R>* x, C2<R>* y, C2<R>* zout, const R* post,
-                      double2 alpha, const C2<R>* aux, double2 beta, const R* mid, int nrhs,
-                      const int* gate) {
-  if (L.mode_perm.empty() || !stream_supported(L)) {
-    set_error("basis pair: needs the block form of U (nx in {8, 12, 16})");
-    return UFG_EINVAL;
-  }
-  if (x == nullptr || y == nullptr || (zout != nullptr && (zout == x || zout == y))) {
-    set_error("basis pair: bad vectors");
-    return UFG_EINVAL;
-  }
-  PairArgs<R> a;
-  a.src = x;
-  a.dst = y;
-  a.zout = zout;
-  a.post = post;
-  a.mid = mid;
-  a.alpha = alpha;
-  a.beta = beta;
-  a.aux = (beta.x == 0.0 && beta.y == 0.0) ? nullptr : aux;
-  a.gate = gate;
-  a.nrhs = nrhs;
-  switch (L.nx) {
-    case 8: return launch_basis_pair_nx<R, 8>(L, a);
-    case 12: return launch_basis_pair_nx<R, 12>(L, a);
-    case 16: return launch_basis_pair_nx<R, 16>(L, a);
-    default: set_error("basis pair: unsupported nx"); return UFG_EINVAL;
-  }
-}
-
-template int launch_basis_pair<float>(const Lattice&, const float2*, float2*, float2*,
-                                      const float*, double2, const float2*, double2,
-                                      const float*, int, const int*);
-template int launch_basis_pair<double>(const Lattice&, const double2*, double2*, double2*,
-                                       const double*, double2, const double2*, double2,
-                                       const double*, int, const int*);
-template int launch_basis_stream<float>(const Lattice&, const HopArgs<float>&, bool);
-template int launch_basis_stream<double>(const Lattice&, const HopArgs<double>&, bool);
 template int launch_hop_stream<float>(const Lattice&, const HopArgs<float>&);
 template int launch_hop_stream<double>(const Lattice&, const HopArgs<double>&);
 

@@ -1,0 +1,586 @@
+// Weak-coupling series W_d (paper, Sec. 3) on lattices with the block form of
+// the eigenbasis U of T (dimension 3, Nx in {8, 12, 16}).
+//
+// M0^{-1} = U^3 (1 - lam Z)^{-1} U^3T: a basis change per time slice, the
+// antiperiodic recurrence u_t = v_t + lam u_{t-1}, u_{-1} = -u_{Ntau-1} per mode,
+// and the change back. The recurrence is not a pass of its own: a workgroup
+// walks a slab of consecutive slices in sweep order, a thread keeps one z-line
+// of modes, so
+//   - the launch that changes to the modes writes v_t and, in registers, runs
+//     the slab's recurrence from zero; only its last value g (one slice per
+//     slab) is stored;
+//   - wce_scan_kernel turns the g of all slabs into the value before each slab
+//     (U_j = g_j + lam^len U_{j-1}, closed antiperiodically), in FP64;
+//   - the launch that changes back runs the recurrence from that value while
+//     it loads v_t.
+// (1 - lam Z)^{-1} - 1, which the series needs, is lam u_{t-1} directly. The
+// adjoint runs the same on reversed time. Consecutive orders of the series
+// meet as "change back, per-site factors, change to the modes", one launch
+// (PAIR). The order-2 application is FIRST, PAIR, PAIR, LAST with a scan
+// between them: 11 vector passes and 3 small scans, where a temporal solve as
+// a launch of its own (3 passes each) needed 20.
+#include <algorithm>
+#include <cmath>
+
+#include "slice_t3.h"
+#include "wce.h"
+
+namespace ufg {
+namespace {
+
+// Every map of the series is real, so the two components of a vector are
+// independent problems: between the first and the last change the vectors (v,
+// u_0, the carries) are planar, [rhs][t][component][site], and a PAIR workgroup
+// takes one component of a slab. That halves its registers and its LDS slice
+// against complex elements, and its slices are latency-bound otherwise (16^3 x
+// 400, 8 rhs, complex: 2 (complex64) or 1 (complex128) workgroups per CU).
+
+// What a PAIR launch does between its two changes.
+enum PairEpi {
+  kStore = 0,  // forward, first order: z = alpha w stored, sin sigma z goes on
+  kFwd = 1,    // forward: sin sigma (alpha w + beta aux) goes on
+  kAdj = 2     // adjoint: alpha sin sigma w + beta aux goes on (aux complex)
+};
+
+template <typename R>
+struct WceArgs {
+  R* carry = nullptr;         // [nrhs][nslab][2][V]: in before a slab, out after it
+  R* modes = nullptr;         // [nrhs][ntau][2][V]
+  const R* lam = nullptr;     // mode eigenvalues [V]
+  int subtract = 0;           // (1 - lam Z)^{-1} - 1 instead of (1 - lam Z)^{-1}
+  int adjoint = 0;
+  int nrhs = 1;
+  int slab = 1;
+  const int* gate = nullptr;
+  // FIRST: source, or the fused BiCGStab source (PcSource)
+  const C2<R>* src = nullptr;
+  const C2<R>* fr = nullptr;
+  const C2<R>* fp = nullptr;
+  const C2<R>* fv = nullptr;
+  C2<R>* fpnew = nullptr;
+  const void* st = nullptr;
+  // PAIR, LAST
+  R alpha = R(1), beta = R(0);
+  const R* field = nullptr;     // sin sigma
+  const R* u0 = nullptr;        // planar auxiliary term
+  R* zout = nullptr;            // planar z
+  const C2<R>* aux = nullptr;   // complex auxiliary term (kAdj)
+  C2<R>* dst = nullptr;         // LAST
+};
+
+// Workgroup -> (column of `ncol`, slab): contiguous runs of (slab, column) per
+// XCD with the column fastest, so that a slab's field is read through one
+// XCD's L2.
+__device__ __forceinline__ void wce_item(int ncol, int& c, int& sb) {
+  int lid = blockIdx.x;
+  const int full = (int)gridDim.x & ~7;
+  if (lid < full) lid = (lid & 7) * (full >> 3) + (lid >> 3);
+  c = lid % ncol;
+  sb = lid / ncol;
+}
+
+// U^3T x per slice, and the slab's recurrence from zero.
+template <typename R, int NX, int SRC>
+__global__ void __launch_bounds__(NX * NX, sizeof(R) == 8 && NX == 16 ? 2 : 1)
+    wce_first_kernel(WceArgs<R> a, CoefPtr<R, NX> cf, int ntau, int nslab) {
+  constexpr int P = NX * NX, V = NX * NX * NX;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  C2<R>* lds = reinterpret_cast<C2<R>*>(smem_raw);
+  int r, sb;
+  wce_item(a.nrhs, r, sb);
+  if (a.gate && a.gate[r] == 0) return;
+  const unsigned l = threadIdx.x;
+  const int t0 = sb * a.slab, t1 = min(t0 + a.slab, ntau);
+  const SrcScal<R> q = src_scalars<R, SRC>(a.st, r);
+  constexpr int RS = sizeof(R);
+  const auto rl = make_rsrc(a.lam, V * RS);
+  C2<R> W[NX];
+#pragma unroll
+  for (int z = 0; z < NX; ++z) W[z] = zero_of<C2<R>>();
+  constexpr int ES = sizeof(C2<R>);
+  auto load = [&](int k, auto& Y) {
+    const int t = a.adjoint ? t1 - 1 - (k - t0) : k;
+    const auto rs = make_rsrc(a.src + ((long long)r * ntau + t) * V, V * ES);
+#pragma unroll
+    for (int z = 0; z < NX; ++z) Y[z] = bload<R>(rs, l * ES, z * P * ES);
+  };
+  // the next slice in flight during the transform, for FP64 slices of Nx = 16
+  // only, two workgroups of which fill a CU's LDS (16^3 x 400, 8 rhs: 103 -> 87
+  // us; complex64 57 -> 56 us, Nx = 12 slower by the registers it takes)
+  constexpr bool kPre = SRC == 0 && sizeof(R) == 8 && NX == 16;
+  C2<R> N[kPre ? NX : 1];
+  if constexpr (kPre) load(t0, N);
+  for (int k = t0; k < t1; ++k) {
+    const int t = a.adjoint ? t1 - 1 - (k - t0) : k;
+    const long long o = ((long long)r * ntau + t) * V;
+    C2<R> X[NX];
+    if constexpr (kPre) {
+#pragma unroll
+      for (int z = 0; z < NX; ++z) X[z] = N[z];
+      if (k + 1 < t1) load(k + 1, N);
+    } else if constexpr (SRC == 0) {
+      load(k, X);
+    } else {
+      const auto rr = make_rsrc(a.fr + o, V * ES), rv = make_rsrc(a.fv + o, V * ES);
+      const auto rp = make_rsrc(SRC == 1 ? a.fp + o : nullptr, V * ES);
+      const auto rn = make_rsrc(a.fpnew + o, V * ES);
+#pragma unroll
+      for (int z = 0; z < NX; ++z) {
+        const int so = z * P * ES;
+        const C2<R> r0 = bload<R>(rr, l * ES, so), v0 = bload<R>(rv, l * ES, so);
+        if constexpr (SRC == 1) {
+          const C2<R> p0 = bload<R>(rp, l * ES, so);
+          const R dx = p0.x - (q.wr * v0.x - q.wi * v0.y);
+          const R dy = p0.y - (q.wr * v0.y + q.wi * v0.x);
+          X[z] = C2<R>{r0.x + q.br * dx - q.bi * dy, r0.y + q.br * dy + q.bi * dx};
+        } else {
+          X[z] = C2<R>{r0.x - (q.ar * v0.x - q.ai * v0.y), r0.y - (q.ar * v0.y + q.ai * v0.x)};
+        }
+      }
+#pragma unroll
+      for (int z = 0; z < NX; ++z) bstore<R, false>(X[z], a.fpnew + o, rn, l * ES, z * P * ES);
+    }
+    slice_T3<R, NX, 1>(cf, lds, l, X);
+    const auto rd = make_rsrc(a.modes + 2 * o, 2 * V * RS);
+#pragma unroll
+    for (int z = 0; z < NX; ++z) {
+      const R lam = bload_real<R>(rl, l * RS, z * P * RS);
+      W[z] = C2<R>{X[z].x + lam * W[z].x, X[z].y + lam * W[z].y};
+    }
+#pragma unroll
+    for (int z = 0; z < NX; ++z) {
+      bstore_real<R>(X[z].x, rd, l * RS, z * P * RS);
+      bstore_real<R>(X[z].y, rd, l * RS, (V + z * P) * RS);
+    }
+  }
+  const auto rc = make_rsrc(a.carry + ((long long)r * nslab + sb) * 2 * V, 2 * V * RS);
+#pragma unroll
+  for (int z = 0; z < NX; ++z) {
+    bstore_real<R>(W[z].x, rc, l * RS, z * P * RS);
+    bstore_real<R>(W[z].y, rc, l * RS, (V + z * P) * RS);
+  }
+}
+
+// The recurrence of one component from the slab's carry, U^3, the factors
+// between two orders, U^3T, and the next recurrence from zero; in place.
+template <typename R, int NX, int EPI>
+__global__ void __launch_bounds__(NX * NX)
+    wce_pair_kernel(WceArgs<R> a, CoefPtr<R, NX> cb, CoefPtr<R, NX> cf, int ntau, int nslab) {
+  constexpr int P = NX * NX, V = NX * NX * NX;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  R* lds = reinterpret_cast<R*>(smem_raw);
+  int rc, sb;
+  wce_item(2 * a.nrhs, rc, sb);
+  const int r = rc >> 1, comp = rc & 1;
+  if (a.gate && a.gate[r] == 0) return;
+  const unsigned l = threadIdx.x;
+  const int t0 = sb * a.slab, t1 = min(t0 + a.slab, ntau);
+  constexpr int RS = sizeof(R);
+  const int vo = threadIdx.x * RS;
+  const auto rl = make_rsrc(a.lam, V * RS);
+  const auto rcar = make_rsrc(a.carry + (((long long)r * nslab + sb) * 2 + comp) * V, V * RS);
+  R U[NX], W[NX];
+#pragma unroll
+  for (int z = 0; z < NX; ++z) {
+    U[z] = bload_real<R>(rcar, vo, z * P * RS);
+    W[z] = R(0);
+  }
+  for (int k = t0; k < t1; ++k) {
+    const int t = a.adjoint ? t1 - 1 - (k - t0) : k;
+    const long long o = ((long long)r * ntau + t) * V;
+    const long long op = 2 * o + comp * V;  // planar offset
+    const auto rm = make_rsrc(a.modes + op, V * RS);
+    R X[NX];
+#pragma unroll
+    for (int z = 0; z < NX; ++z) X[z] = bload_real<R>(rm, vo, z * P * RS);
+#pragma unroll
+    for (int z = 0; z < NX; ++z) {
+      const R d = bload_real<R>(rl, vo, z * P * RS) * U[z];
+      U[z] = X[z] + d;
+      X[z] = a.subtract ? d : U[z];
+    }
+    R F[NX], A[EPI != kStore ? NX : 1];
+    const auto rf = make_rsrc(a.field + (long long)t * V, V * RS);
+#pragma unroll
+    for (int z = 0; z < NX; ++z) F[z] = bload_real<R>(rf, vo, z * P * RS);
+    if constexpr (EPI == kFwd) {
+      const auto ru = make_rsrc(a.u0 + op, V * RS);
+#pragma unroll
+      for (int z = 0; z < NX; ++z) A[z] = bload_real<R>(ru, vo, z * P * RS);
+    } else if constexpr (EPI == kAdj) {
+      const auto ru = make_rsrc(reinterpret_cast<const R*>(a.aux + o) + comp, 2 * V * RS);
+#pragma unroll
+      for (int z = 0; z < NX; ++z) A[z] = bload_real<R>(ru, 2 * vo, 2 * z * P * RS);
+    }
+    slice_T3<R, NX, 2>(cb, lds, l, X);  // U^3
+#pragma unroll
+    for (int z = 0; z < NX; ++z) {
+      R w = (EPI == kAdj ? a.alpha * F[z] : a.alpha) * X[z];
+      if constexpr (EPI != kStore) w += a.beta * A[EPI != kStore ? z : 0];
+      X[z] = EPI == kAdj ? w : F[z] * w;
+      if constexpr (EPI == kStore) {
+        const auto rz = make_rsrc(a.zout + op, V * RS);
+        bstore_real<R>(w, rz, vo, z * P * RS);
+      }
+    }
+    slice_T3<R, NX, 1>(cf, lds, l, X);  // U^3T
+#pragma unroll
+    for (int z = 0; z < NX; ++z) W[z] = X[z] + bload_real<R>(rl, vo, z * P * RS) * W[z];
+#pragma unroll
+    for (int z = 0; z < NX; ++z) bstore_real<R>(X[z], rm, vo, z * P * RS);
+  }
+#pragma unroll
+  for (int z = 0; z < NX; ++z) bstore_real<R>(W[z], rcar, vo, z * P * RS);
+}
+
+// The recurrence from the slab's carry and U^3: y = alpha U^3 u (+ beta u0).
+template <typename R, int NX, bool AUX>
+__global__ void __launch_bounds__(NX * NX, sizeof(R) == 8 && NX == 16 ? 2 : 1)
+    wce_last_kernel(WceArgs<R> a, CoefPtr<R, NX> cb, int ntau, int nslab) {
+  constexpr int P = NX * NX, V = NX * NX * NX;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  C2<R>* lds = reinterpret_cast<C2<R>*>(smem_raw);
+  int r, sb;
+  wce_item(a.nrhs, r, sb);
+  if (a.gate && a.gate[r] == 0) return;
+  const unsigned l = threadIdx.x;
+  const int t0 = sb * a.slab, t1 = min(t0 + a.slab, ntau);
+  constexpr int RS = sizeof(R), ES = sizeof(C2<R>);
+  const int vo = threadIdx.x * RS;
+  const auto rl = make_rsrc(a.lam, V * RS);
+  const auto rc = make_rsrc(a.carry + ((long long)r * nslab + sb) * 2 * V, 2 * V * RS);
+  C2<R> U[NX];
+#pragma unroll
+  for (int z = 0; z < NX; ++z)
+    U[z] = C2<R>{bload_real<R>(rc, vo, z * P * RS), bload_real<R>(rc, vo, (V + z * P) * RS)};
+  for (int k = t0; k < t1; ++k) {
+    const int t = a.adjoint ? t1 - 1 - (k - t0) : k;
+    const long long o = ((long long)r * ntau + t) * V;
+    const auto rm = make_rsrc(a.modes + 2 * o, 2 * V * RS);
+    C2<R> X[NX];
+#pragma unroll
+    for (int z = 0; z < NX; ++z)
+      X[z] = C2<R>{bload_real<R>(rm, vo, z * P * RS), bload_real<R>(rm, vo, (V + z * P) * RS)};
+#pragma unroll
+    for (int z = 0; z < NX; ++z) {
+      const R lam = bload_real<R>(rl, vo, z * P * RS);
+      const C2<R> d = C2<R>{lam * U[z].x, lam * U[z].y};
+      U[z] = C2<R>{X[z].x + d.x, X[z].y + d.y};
+      X[z] = a.subtract ? d : U[z];
+    }
+    slice_T3<R, NX, 2>(cb, lds, l, X);
+    C2<R> A[AUX ? NX : 1];
+    if constexpr (AUX) {
+      const auto ru = make_rsrc(a.u0 + 2 * o, 2 * V * RS);
+#pragma unroll
+      for (int z = 0; z < NX; ++z)
+        A[z] = C2<R>{bload_real<R>(ru, vo, z * P * RS), bload_real<R>(ru, vo, (V + z * P) * RS)};
+    }
+    const auto rd = make_rsrc(a.dst + o, V * ES);
+#pragma unroll
+    for (int z = 0; z < NX; ++z) {
+      C2<R> w = C2<R>{a.alpha * X[z].x, a.alpha * X[z].y};
+      if constexpr (AUX) {
+        w.x += a.beta * A[AUX ? z : 0].x;
+        w.y += a.beta * A[AUX ? z : 0].y;
+      }
+      bstore<R, false>(w, a.dst + o, rd, threadIdx.x * ES, z * P * ES);
+    }
+  }
+}
+
+__device__ __forceinline__ double ipow(double x, int n) {
+  double r = 1.0;
+  for (; n > 0; n >>= 1) {
+    if (n & 1) r *= x;
+    x *= x;
+  }
+  return r;
+}
+
+// Per (rhs, component, mode): the slab ends g_j (each slab's recurrence from
+// zero, in sweep order) become the values before each slab: U_j = g_j +
+// lam^len_j U_{j-1}, U_{-1} = -U_last. MODES columns along the lanes x CHUNKS
+// chunks of slabs per workgroup; a chunk of up to KEEP slabs stays in registers
+// between the two sweeps. Every thread walks all chunk sums by itself (one
+// barrier, no serial section of one chunk's threads). FP64 whatever the vector
+// type.
+template <typename R, int MODES, int CHUNKS>
+__global__ void __launch_bounds__(MODES* CHUNKS)
+    wce_scan_kernel(R* carry, const double* __restrict__ lam_mode, int V, int ntau, int slab,
+                    int nslab, int nrhs, int adjoint, const int* gate) {
+  constexpr int KEEP = sizeof(R) == 4 ? 16 : 8;
+  __shared__ double cend[CHUNKS][MODES];
+  __shared__ double cpow[CHUNKS][MODES];
+  const int ml = threadIdx.x % MODES, c = threadIdx.x / MODES;
+  const long long gid = (long long)blockIdx.x * MODES + ml;
+  const bool inb = gid < 2ll * V * nrhs;
+  const int rc = inb ? int(gid / V) : 0;
+  const int n = inb ? int(gid - (long long)rc * V) : 0;
+  const bool act = inb && !(gate && gate[rc >> 1] == 0);
+  const int Lc = (nslab + CHUNKS - 1) / CHUNKS;
+  const int k0 = min(c * Lc, nslab), k1 = min(k0 + Lc, nslab);
+  const int short_k = adjoint ? 0 : nslab - 1;  // sweep position of the slab that may be short
+  R* col = carry + (((long long)(rc >> 1) * nslab) * 2 + (rc & 1)) * V + n;
+  auto at = [&](int k) -> long long { return (long long)(adjoint ? nslab - 1 - k : k) * 2 * V; };
+  double lamS = 0.0, lamL = 0.0, pw = 1.0, w = 0.0;
+  R G[KEEP];
+  if (act) {
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i)
+      if (k0 + i < k1) G[i] = col[at(k0 + i)];
+    const double lam = lam_mode[n];
+    lamS = ipow(lam, slab);
+    lamL = ipow(lam, ntau - (nslab - 1) * slab);
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i) {
+      if (k0 + i < k1) {
+        const double p = k0 + i == short_k ? lamL : lamS;
+        w = double(G[i]) + p * w;
+        pw *= p;
+      }
+    }
+#pragma unroll 4
+    for (int k = k0 + KEEP; k < k1; ++k) {
+      const double p = k == short_k ? lamL : lamS;
+      w = double(col[at(k)]) + p * w;
+      pw *= p;
+    }
+  }
+  cend[c][ml] = w;
+  cpow[c][ml] = pw;
+  __syncthreads();
+  if (!act) return;
+  // U: the scan over all chunks from zero; v, pv: its value and power before chunk c
+  double U = 0.0, v = 0.0, lamN = 1.0, pv = 1.0;
+#pragma unroll 8
+  for (int j = 0; j < CHUNKS; ++j) {
+    if (j == c) {
+      v = U;
+      pv = lamN;
+    }
+    const double p = cpow[j][ml];
+    U = cend[j][ml] + p * U;
+    lamN *= p;
+  }
+  v -= pv * U / (1.0 + lamN);  // U_{-1} = -U / (1 + lam^Ntau), carried to chunk c
+#pragma unroll
+  for (int i = 0; i < KEEP; ++i) {
+    if (k0 + i < k1) {
+      const double p = k0 + i == short_k ? lamL : lamS;
+      col[at(k0 + i)] = R(v);
+      v = double(G[i]) + p * v;
+    }
+  }
+#pragma unroll 4
+  for (int k = k0 + KEEP; k < k1; ++k) {
+    const long long i = at(k);
+    const R g = col[i];
+    const double p = k == short_k ? lamL : lamS;
+    col[i] = R(v);
+    v = double(g) + p * v;
+  }
+}
+
+template <typename R, int MODES, int CHUNKS>
+int launch_scan_shape(const Lattice& L, R* carry, int slab, int nslab, int nrhs, bool adjoint,
+                      const int* gate) {
+  const long long n = 2ll * L.V * nrhs;
+  hipLaunchKernelGGL((wce_scan_kernel<R, MODES, CHUNKS>), dim3((unsigned)((n + MODES - 1) / MODES)),
+                     dim3(MODES * CHUNKS), 0, L.stream, carry, L.f64.lam, L.V, L.ntau, slab, nslab,
+                     nrhs, adjoint ? 1 : 0, gate);
+  UFG_HIP(hipGetLastError());
+  return UFG_OK;
+}
+
+template <typename R>
+int launch_scan(const Lattice& L, R* carry, int slab, int nslab, int nrhs, bool adjoint,
+                const int* gate) {
+  if (2ll * L.V * nrhs >= 64 * 256)
+    return launch_scan_shape<R, 64, 8>(L, carry, slab, nslab, nrhs, adjoint, gate);
+  return launch_scan_shape<R, 16, 32>(L, carry, slab, nslab, nrhs, adjoint, gate);
+}
+
+// The blocks of U^T and U, adjacent on the device.
+template <typename R, int NX>
+CoefPtr<R, NX> coef_fwd(const Lattice& L) {
+  return {reinterpret_cast<const SplitCoef<R, NX>*>(fields<R>(L).modes)};
+}
+template <typename R, int NX>
+CoefPtr<R, NX> coef_bwd(const Lattice& L) {
+  return {reinterpret_cast<const SplitCoef<R, NX>*>(fields<R>(L).modes) + 1};
+}
+
+// One instantiation per kernel: the LDS attribute is set once.
+#define WCE_LAUNCH(KERNEL, ES, GRID, ...)                                                      \
+  do {                                                                                         \
+    const size_t lds = size_t(lds_slice_elems<NX>()) * (ES);                                   \
+    static bool attr = false;                                                                  \
+    if (!attr) {                                                                               \
+      UFG_HIP(hipFuncSetAttribute((const void*)KERNEL,                                         \
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));      \
+      attr = true;                                                                             \
+    }                                                                                          \
+    hipLaunchKernelGGL(KERNEL, dim3((unsigned)(GRID)), dim3(NX * NX), lds, L.stream,           \
+                       __VA_ARGS__, L.ntau, nslab);                                            \
+    UFG_HIP(hipGetLastError());                                                                \
+    return UFG_OK;                                                                             \
+  } while (0)
+
+template <typename R, int NX, int SRC>
+int launch_first(const Lattice& L, const WceArgs<R>& a, int nslab) {
+  WCE_LAUNCH((wce_first_kernel<R, NX, SRC>), sizeof(C2<R>), nslab * a.nrhs, a,
+             (coef_fwd<R, NX>(L)));
+}
+template <typename R, int NX, int EPI>
+int launch_pair(const Lattice& L, const WceArgs<R>& a, int nslab) {
+  WCE_LAUNCH((wce_pair_kernel<R, NX, EPI>), sizeof(R), nslab * a.nrhs * 2, a,
+             (coef_bwd<R, NX>(L)), (coef_fwd<R, NX>(L)));
+}
+template <typename R, int NX, bool AUX>
+int launch_last(const Lattice& L, const WceArgs<R>& a, int nslab) {
+  WCE_LAUNCH((wce_last_kernel<R, NX, AUX>), sizeof(C2<R>), nslab * a.nrhs, a,
+             (coef_bwd<R, NX>(L)));
+}
+#undef WCE_LAUNCH
+
+#define WCE_NX(CALL)                                                             \
+  switch (L.nx) {                                                                \
+    case 8: return CALL(8);                                                      \
+    case 12: return CALL(12);                                                    \
+    case 16: return CALL(16);                                                    \
+    default: set_error("weak-coupling kernels: unsupported nx"); return UFG_EINVAL; \
+  }
+
+template <typename R>
+int first_change(const Lattice& L, const WceArgs<R>& a, int src_mode, int nslab) {
+#define WCE_F(N)                                                       \
+  (src_mode == 1   ? launch_first<R, N, 1>(L, a, nslab)                \
+   : src_mode == 2 ? launch_first<R, N, 2>(L, a, nslab)                \
+                   : launch_first<R, N, 0>(L, a, nslab))
+  WCE_NX(WCE_F)
+#undef WCE_F
+}
+template <typename R>
+int pair_change(const Lattice& L, const WceArgs<R>& a, int epi, int nslab) {
+#define WCE_P(N)                                                       \
+  (epi == kStore ? launch_pair<R, N, kStore>(L, a, nslab)              \
+   : epi == kFwd ? launch_pair<R, N, kFwd>(L, a, nslab)                \
+                 : launch_pair<R, N, kAdj>(L, a, nslab))
+  WCE_NX(WCE_P)
+#undef WCE_P
+}
+template <typename R>
+int last_change(const Lattice& L, const WceArgs<R>& a, int nslab) {
+#define WCE_L(N) (a.u0 ? launch_last<R, N, true>(L, a, nslab) : launch_last<R, N, false>(L, a, nslab))
+  WCE_NX(WCE_L)
+#undef WCE_L
+}
+
+}  // namespace
+
+int wce_slab(const Lattice& L, int nrhs) {
+  if (L.nslab > 0) return (L.ntau + L.nslab - 1) / L.nslab;  // nslab <= ntau
+  if (L.slab > 0) return std::min(L.slab, L.ntau);
+  // Longer slabs make the scan cheaper (its traffic is 1 / slab of a pass) and
+  // each launch longer (a slab's slices run one after the other); with n slices
+  // in all the balance lies near sqrt(n / 128). Order-2 application, us at slab
+  // 1 / 2 / 4 / 5 / 8: 16^3 x 400, 8 rhs (n = 3200) complex64 456 / 347 / 299 /
+  // 282 / 301, complex128 969 / 707 / 638 / 596 / 625; 12^3 x 200, 8 rhs (1600)
+  // complex128 184 / 155 / 146 / 154 / 181; 8^3 x 160, 4 rhs (640) 50 / 47 / 53 /
+  // 56 / 71; 16^3 x 400, 1 rhs (400) complex64 96 / 89 / 105 / 117 / 161; 12^3 x
+  // 200, 1 rhs (200) complex128 62 / 66 / 92 / 104 / 152.
+  const double n = (double)L.ntau * nrhs;
+  return std::min(8, std::max(1, (int)std::lround(std::sqrt(n / 128.0))));
+}
+
+template <typename R>
+int wce_modes_apply(Lattice& L, const PcPlan& pc, bool adjoint, const C2<R>* x, C2<R>* y,
+                    int nrhs, const int* gate, Counters* cnt, const PcSource<R>* src) {
+  const Fields<R>& F = fields<R>(L);
+  const int d = pc.order;
+  int rc = 0;
+  WceArgs<R> a;
+  a.modes = reinterpret_cast<R*>(slot_vec<R>(L, SLOT_PC0 + 0, nrhs, &rc));
+  UFG_TRY(rc);
+  // one slice per slab: at most a vector
+  a.carry = reinterpret_cast<R*>(slot_vec<R>(L, SLOT_PC0 + 1, nrhs, &rc));
+  UFG_TRY(rc);
+  R* u0 = nullptr;
+  if (!adjoint && d > 0) {
+    u0 = reinterpret_cast<R*>(slot_vec<R>(L, SLOT_PC0 + 2, nrhs, &rc));
+    UFG_TRY(rc);
+  }
+  a.lam = F.lam;
+  a.field = F.sn;
+  a.nrhs = nrhs;
+  a.slab = wce_slab(L, nrhs);
+  a.adjoint = adjoint ? 1 : 0;
+  a.gate = gate;
+  const int nslab = (L.ntau + a.slab - 1) / a.slab;
+  auto scan = [&]() -> int {
+    cnt->m0inv += 1;
+    return launch_scan<R>(L, a.carry, a.slab, nslab, nrhs, adjoint, gate);
+  };
+  a.src = x;
+  if (src) {
+    if (src->out != x) {
+      set_error("weak-coupling apply: the fused source must be stored to x");
+      return UFG_EINVAL;
+    }
+    a.fr = src->r;
+    a.fp = src->p;
+    a.fv = src->v;
+    a.fpnew = src->out;
+    a.st = src->st;
+  }
+  UFG_TRY(first_change<R>(L, a, src ? src->mode : 0, nslab));
+  UFG_TRY(scan());
+  a.dst = y;
+  a.alpha = R(1);
+  if (d == 0) {
+    a.alpha = R(pc.w[0]);
+    return last_change<R>(L, a, nslab);
+  }
+  double scale = pc.w[d];
+  if (!adjoint) {
+    // u_0 = M0^{-1} x, kept for z_m = w_m u_0 + K z_{m+1}; the modes then hold
+    // U^3T (sin sigma z_{m+1}) up to `scale`
+    a.zout = u0;
+    UFG_TRY(pair_change<R>(L, a, kStore, nslab));
+    UFG_TRY(scan());
+    a.u0 = u0;
+    a.subtract = 1;
+    for (int m = d - 1; m >= 0; --m) {
+      cnt->mv += 1;
+      a.alpha = R(L.A * scale);
+      a.beta = R(pc.w[m]);
+      if (m == 0) break;
+      UFG_TRY(pair_change<R>(L, a, kFwd, nslab));
+      UFG_TRY(scan());
+      scale = 1.0;
+    }
+    return last_change<R>(L, a, nslab);
+  }
+  // z_m = w_m x + K' z_{m+1}, K' v = A S U^3 [(1 - lam Z^T)^{-1} - 1] U^3T v; y = M0^{-T} z_0
+  a.aux = x;
+  a.subtract = 1;
+  for (int m = d - 1; m >= 0; --m) {
+    cnt->mv += 1;
+    a.alpha = R(L.A * scale);
+    a.beta = R(pc.w[m]);
+    UFG_TRY(pair_change<R>(L, a, kAdj, nslab));
+    UFG_TRY(scan());
+    scale = 1.0;
+  }
+  a.alpha = R(1);
+  a.subtract = 0;
+  return last_change<R>(L, a, nslab);
+}
+
+template int wce_modes_apply<float>(Lattice&, const PcPlan&, bool, const float2*, float2*, int,
+                                    const int*, Counters*, const PcSource<float>*);
+template int wce_modes_apply<double>(Lattice&, const PcPlan&, bool, const double2*, double2*, int,
+                                     const int*, Counters*, const PcSource<double>*);
+
+}  // namespace ufg

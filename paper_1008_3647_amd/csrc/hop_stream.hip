@@ -323,8 +323,18 @@ __device__ __forceinline__ double wsum(double v) {
 // TR = 1: the transform's y and x stages on MFMA (complex64, Nx = 16, plain
 // operator only; see slice_T3_mfma16); TR = 2: every stage through 16-point
 // DFTs (same restriction; see slice_T3_fft16).
+// At most three waves per SIMD for the complex64 Nx = 16 M^T with scaling and
+// auxiliary term: aiming at the four that its LDS slice allows, the compiler
+// spills (123 VGPRs and scratch; a degree-8 Chebyshev application on 16^3 x 217,
+// 5 rhs 347 -> 367 us).
+template <typename R, int NX, int DIR, bool GENERAL>
+constexpr int hop_max_waves() {
+  return sizeof(R) == 4 && NX == 16 && DIR > 0 && GENERAL ? 3 : 8;
+}
+
 template <typename R, int NX, int DIR, bool GENERAL, int SRC, int RED, int TR = 0>
 __global__ void __launch_bounds__(NX * NX)
+    __attribute__((amdgpu_waves_per_eu(1, hop_max_waves<R, NX, DIR, GENERAL>())))
     hop_stream_kernel(HopArgs<R> a, SplitCoef<R, NX> c, int ntau, int nslab, int xg, int ri) {
   static_assert(TR == 0 || (sizeof(R) == 4 && NX == 16 && SRC == 0 && RED == 0 && !GENERAL),
                 "the MFMA and DFT transform routes exist for the plain complex64 Nx = 16 "

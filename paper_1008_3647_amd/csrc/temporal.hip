@@ -7,6 +7,7 @@
 //     u = (1 + lam^Ntau)^{-1} sum_m lam^m Z^m v, evaluated by two sweeps).
 // One thread owns one (rhs, site) column; consecutive threads take consecutive
 // sites so every access along t is a coalesced row.
+#include "slice_t3.h"
 #include "ufg_internal.h"
 
 namespace ufg {
@@ -70,53 +71,166 @@ __global__ void sca_setup_kernel(const double* __restrict__ b, int V, int ntau, 
 }
 
 // x = L^{-1} D^{-1} L^{dagger -1} v per site. x may alias v.
-template <typename R>
-__global__ void sca_apply_kernel(const C2<R>* v, C2<R>* x, const R* __restrict__ D,
-                                 const R* __restrict__ Lb, int V, int ntau, int nrhs,
-                                 const int* gate) {
-  const long long gid = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  if (gid >= (long long)V * nrhs) return;
-  const int r = int(gid / V);
-  const int n = int(gid - (long long)r * V);
-  if (gate && gate[r] == 0) return;
-  const long long base = (long long)r * ntau * V + n;
-  // forward sweep: w_0 = v_0, w_t = v_t + L_{t-1} w_{t-1}, corner on the last slice
-  C2<R> w0 = v[base];
-  C2<R> w = w0;
-  x[base] = C2<R>{w0.x / D[n], w0.y / D[n]};
-  for (int t = 1; t < ntau; ++t) {
-    const long long i = base + (long long)t * V;
-    const long long f = (long long)t * V + n;
-    const R l = Lb[f - V];
-    const C2<R> vt = v[i];
-    C2<R> wt = C2<R>{vt.x + l * w.x, vt.y + l * w.y};
-    if (t == ntau - 1) {
-      const R lc = Lb[(long long)(ntau - 1) * V + n];
-      wt.x -= lc * w0.x;
-      wt.y -= lc * w0.y;
-    }
-    w = wt;
-    const R d = D[f];
-    x[i] = C2<R>{wt.x / d, wt.y / d};
+//   forward : w_0 = v_0, w_t = v_t + L_{t-1} w_{t-1}, w_{Ntau-1} also - L_{Ntau-1} w_0
+//   backward: x_{Ntau-1} = w_{Ntau-1} / D, x_t = w_t / D_t + L_t x_{t+1}, x_0 also
+//             - L_{Ntau-1} x_{Ntau-1}
+// Every factor is real, so a thread owns one real component; a column's time
+// line is split into CHUNKS chunks. Each sweep runs a chunk from zero, the
+// chunk ends are combined (in FP64) through LDS into the value before each
+// chunk, and the chunk runs again from it. KMAX > 0: a chunk of at most KMAX
+// slices stays in registers from the load of v to the store of x, one read and
+// one write of the vector; KMAX = 0 (longer time lines): the sweeps re-read v
+// and x. A single thread per column (the earlier form) was bound by its chain
+// of 2 Ntau dependent accesses on few waves.
+template <typename R, int LANES, int CHUNKS, int KMAX>
+__global__ void __launch_bounds__(LANES* CHUNKS)
+    sca_apply_kernel(const R* v, R* x, const R* __restrict__ D, const R* __restrict__ Lb, int V,
+                     int ntau, int nrhs, const int* gate) {
+  __shared__ double cend[2][CHUNKS][LANES], cpow[2][CHUNKS][LANES];
+  __shared__ R xlast[LANES];
+  constexpr bool kReg = KMAX > 0;
+  constexpr int KA = kReg ? KMAX : 1;
+  const int ml = threadIdx.x % LANES, c = threadIdx.x / LANES;
+  const long long gid = (long long)blockIdx.x * LANES + ml;
+  const bool inb = gid < 2ll * V * nrhs;
+  const int r = inb ? int(gid / (2 * V)) : 0;
+  const int e = inb ? int(gid - 2ll * V * r) : 0;
+  const int n = e >> 1;
+  const bool act = inb && !(gate && gate[r] == 0);
+  const int K = (ntau + CHUNKS - 1) / CHUNKS;
+  const int s0 = min(c * K, ntau), cnt = act ? min(s0 + K, ntau) - s0 : 0;
+  const bool first = s0 == 0, last = cnt > 0 && s0 + cnt == ntau;
+  // Register path: raw buffer accesses, the thread's byte offset in one VGPR and
+  // the slice's in an SGPR (the launcher checks that a vector stays below 4 GiB).
+  const long long nv = 2ll * V * ntau * nrhs, nf = (long long)V * ntau;
+  const auto bv = make_rsrc(v, (unsigned)(nv * sizeof(R))), bx = make_rsrc(x, (unsigned)(nv * sizeof(R)));
+  const auto bl = make_rsrc(Lb, (unsigned)(nf * sizeof(R))), bd = make_rsrc(D, (unsigned)(nf * sizeof(R)));
+  const long long v0 = ((long long)r * ntau + s0) * 2 * V + e, f0 = (long long)s0 * V + n;
+  const int vo = (int)(unsigned)(v0 * sizeof(R)), fo = (int)(unsigned)(f0 * sizeof(R));
+  const int vs = 2 * V * (int)sizeof(R), fs = V * (int)sizeof(R);  // one slice
+  auto vin = [&](int i) -> R {
+    if constexpr (kReg)
+      return bload_real<R>(bv, vo, i * vs);
+    else
+      return v[v0 + (long long)i * 2 * V];
+  };
+  auto xin = [&](int i) -> R { return x[v0 + (long long)i * 2 * V]; };
+  auto xout = [&](int i, R u) {
+    if constexpr (kReg)
+      bstore_real<R>(u, bx, vo, i * vs);
+    else
+      x[v0 + (long long)i * 2 * V] = u;
+  };
+  // L_{t-1} and L_t of slice s0 + i (0 outside the line), D_t
+  auto lprev = [&](int i) -> R { return first && i == 0 ? R(0) : Lb[f0 + (long long)(i - 1) * V]; };
+  auto lnext = [&](int i) -> R {
+    if (last && i == cnt - 1) return R(0);
+    if constexpr (kReg)
+      return bload_real<R>(bl, fo, i * fs);
+    else
+      return Lb[f0 + (long long)i * V];
+  };
+  auto dval = [&](int i) -> R {
+    if constexpr (kReg)
+      return bload_real<R>(bd, fo, i * fs);
+    else
+      return D[f0 + (long long)i * V];
+  };
+  R w[KA], l[KA + 1], d[KA];
+  if constexpr (kReg) {
+#pragma unroll
+    for (int i = 0; i < KA; ++i)
+      if (i < cnt) w[i] = vin(i);
+    if (cnt > 0) l[0] = lprev(0);
+#pragma unroll
+    for (int i = 0; i < KA; ++i)
+      if (i < cnt) {
+        l[i + 1] = lnext(i);
+        d[i] = dval(i);
+      }
   }
-  // backward sweep: x_{Ntau-1} = w'_{Ntau-1}; x_t = w'_t + L_t x_{t+1};
-  // x_0 additionally loses L_{Ntau-1} x_{Ntau-1}
-  const long long last = base + (long long)(ntau - 1) * V;
-  const C2<R> xl = x[last];
-  C2<R> xn = xl;
-  for (int t = ntau - 2; t >= 0; --t) {
-    const long long i = base + (long long)t * V;
-    const R l = Lb[(long long)t * V + n];
-    const C2<R> wt = x[i];
-    C2<R> xt = C2<R>{wt.x + l * xn.x, wt.y + l * xn.y};
-    if (t == 0) {
-      const R lc = Lb[(long long)(ntau - 1) * V + n];
-      xt.x -= lc * xl.x;
-      xt.y -= lc * xl.y;
-    }
-    x[i] = xt;
-    xn = xt;
+  const R lc = act && (first || last) ? Lb[(long long)(ntau - 1) * V + n] : R(0);
+  const R corner = last ? lc * v[(long long)r * ntau * 2 * V + e] : R(0);  // read before any store of x
+  if constexpr (kReg) {
+#pragma unroll
+    for (int i = 0; i < KA; ++i)
+      if (last && i == cnt - 1) w[i] -= corner;
   }
+  // element i of the chunk's right-hand side of the forward sweep
+  auto rhs = [&](int i) -> R {
+    if constexpr (kReg)
+      return w[i];
+    else
+      return last && i == cnt - 1 ? vin(i) - corner : vin(i);
+  };
+#define SCA_UP(BODY)                                   \
+  if constexpr (kReg) {                                \
+    _Pragma("unroll") for (int i = 0; i < KA; ++i) {   \
+      if (i < cnt) { BODY }                            \
+    }                                                  \
+  } else {                                             \
+    for (int i = 0; i < cnt; ++i) { BODY }             \
+  }
+#define SCA_DOWN(BODY)                                    \
+  if constexpr (kReg) {                                   \
+    _Pragma("unroll") for (int i = KA - 1; i >= 0; --i) { \
+      if (i < cnt) { BODY }                               \
+    }                                                     \
+  } else {                                                \
+    for (int i = cnt - 1; i >= 0; --i) { BODY }           \
+  }
+  {
+    R g = R(0);
+    R p = R(1);
+    SCA_UP({
+      const R a = kReg ? l[kReg ? i : 0] : lprev(i);
+      g = rhs(i) + a * g;
+      p *= a;
+    })
+    cend[0][c][ml] = double(g);
+    cpow[0][c][ml] = double(p);
+  }
+  __syncthreads();
+  {
+    double U = 0.0;
+    for (int j = 0; j < c; ++j) U = cend[0][j][ml] + cpow[0][j][ml] * U;
+    R u = R(U);
+    SCA_UP({
+      const R a = kReg ? l[kReg ? i : 0] : lprev(i);
+      u = rhs(i) + a * u;
+      const R o = u / (kReg ? d[kReg ? i : 0] : dval(i));
+      if constexpr (kReg)
+        w[kReg ? i : 0] = o;
+      else
+        xout(i, o);
+      if (last && i == cnt - 1) xlast[ml] = o;
+    })
+  }
+  {
+    R g = R(0);
+    R p = R(1);
+    SCA_DOWN({
+      const R b = kReg ? l[kReg ? i + 1 : 0] : lnext(i);
+      g = (kReg ? w[kReg ? i : 0] : xin(i)) + b * g;
+      p *= b;
+    })
+    cend[1][c][ml] = double(g);
+    cpow[1][c][ml] = double(p);
+  }
+  __syncthreads();
+  {
+    double U = 0.0;
+    for (int j = CHUNKS - 1; j > c; --j) U = cend[1][j][ml] + cpow[1][j][ml] * U;
+    R u = R(U);
+    SCA_DOWN({
+      const R b = kReg ? l[kReg ? i + 1 : 0] : lnext(i);
+      u = (kReg ? w[kReg ? i : 0] : xin(i)) + b * u;
+      if (first && i == 0) u -= lc * xlast[ml];
+      xout(i, u);
+    })
+  }
+#undef SCA_UP
+#undef SCA_DOWN
 }
 
 // Per spatial mode n with eigenvalue lam of exp(-tau K):
@@ -227,15 +341,38 @@ int launch_sca_setup(Lattice& L, double alpha) {
   return UFG_OK;
 }
 
-template <typename R>
-int launch_sca_apply(const Lattice& L, const C2<R>* v, C2<R>* x, int nrhs, const int* gate) {
+namespace {
+template <typename R, int LANES, int CHUNKS, int KMAX>
+int launch_sca_shape(const Lattice& L, const C2<R>* v, C2<R>* x, int nrhs, const int* gate) {
   const Fields<R>& F = fields<R>(L);
-  const long long n = (long long)L.V * nrhs;
-  const int threads = 128;
-  hipLaunchKernelGGL((sca_apply_kernel<R>), dim3((unsigned)((n + threads - 1) / threads)),
-                     dim3(threads), 0, L.stream, v, x, F.scaD, F.scaL, L.V, L.ntau, nrhs, gate);
+  const long long n = 2ll * L.V * nrhs;
+  hipLaunchKernelGGL((sca_apply_kernel<R, LANES, CHUNKS, KMAX>),
+                     dim3((unsigned)((n + LANES - 1) / LANES)), dim3(LANES * CHUNKS), 0, L.stream,
+                     reinterpret_cast<const R*>(v), reinterpret_cast<R*>(x), F.scaD, F.scaL, L.V,
+                     L.ntau, nrhs, gate);
   UFG_HIP(hipGetLastError());
   return UFG_OK;
+}
+}  // namespace
+
+template <typename R>
+int launch_sca_apply(const Lattice& L, const C2<R>* v, C2<R>* x, int nrhs, const int* gate) {
+  const int k32 = (L.ntau + 31) / 32, k16 = (L.ntau + 15) / 16;
+  if (sizeof(C2<R>) * (double)L.N * nrhs >= 4294967296.0)  // beyond 32-bit offsets
+    return launch_sca_shape<R, 16, 32, 0>(L, v, x, nrhs, gate);
+  // 512 threads: 16 columns x 32 chunks, or, for complex64 with enough columns
+  // for 1024 workgroups, 32 columns (128-byte rows instead of 64) x 16 chunks:
+  // 16^3 x 400, 8 rhs complex64 117 -> 75 us, complex128 143 -> 142 us. One thread
+  // a column took 319 / 410 us there and 63 us on 8^3 x 160, 4 rhs complex128 (7.3
+  // us now; 16 x 4000, 8 rhs, memory path, 2818 -> 120 us).
+  if (sizeof(R) == 4 && 2ll * L.V * nrhs >= 32 * 1024 && k16 <= 32) {
+    if (k16 <= 16) return launch_sca_shape<R, 32, 16, 16>(L, v, x, nrhs, gate);
+    return launch_sca_shape<R, 32, 16, 32>(L, v, x, nrhs, gate);
+  }
+  if (k32 <= 8) return launch_sca_shape<R, 16, 32, 8>(L, v, x, nrhs, gate);
+  if (k32 <= 16) return launch_sca_shape<R, 16, 32, 16>(L, v, x, nrhs, gate);
+  if (k32 <= 32) return launch_sca_shape<R, 16, 32, 32>(L, v, x, nrhs, gate);
+  return launch_sca_shape<R, 16, 32, 0>(L, v, x, nrhs, gate);
 }
 
 template <typename R>

@@ -131,6 +131,9 @@ static int alloc_fields(Lattice& L) {
   for (auto pp : f)
     if (hipMalloc(pp, N * sizeof(float)) != hipSuccess) return UFG_ENOMEM;
   if (hipMalloc(&L.sigma, N * sizeof(double)) != hipSuccess) return UFG_ENOMEM;
+  if (hipHostMalloc(reinterpret_cast<void**>(&L.bmax_host), sizeof(double),
+                    hipHostMallocDefault) != hipSuccess)
+    return UFG_ENOMEM;
   return UFG_OK;
 }
 
@@ -139,6 +142,7 @@ static void free_fields(Lattice& L) {
                   L.f32.cs, L.f32.scaD, L.f32.scaL, L.sigma, L.f64.T, L.f32.T};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
+  if (L.bmax_host) (void)hipHostFree(L.bmax_host);
 }
 
 // The constants of one precision (T, U, U^T, mode eigenvalues, block forms of U^T
@@ -172,20 +176,15 @@ static int upload_constants(Lattice& L, Fields<R>& F, const std::vector<double>&
   return UFG_OK;
 }
 
-int install_field(Lattice& L) {
+int install_field(Lattice& L, const double* sigma) {
   const int nblk = 512;
   int rc = L.red.ensure(nblk * sizeof(double));
   if (rc) return rc;
   double* part = reinterpret_cast<double*>(L.red.p);
-  UFG_TRY(launch_field_setup(L, part, nblk));
-  std::vector<double> h(nblk);
-  UFG_HIP(hipMemcpyAsync(h.data(), part, nblk * sizeof(double), hipMemcpyDeviceToHost, L.stream));
+  UFG_TRY(launch_field_setup(L, sigma, part, nblk));
+  UFG_TRY(launch_sca_setup(L, 1.0, part, nblk, L.bmax_host));
   UFG_HIP(hipStreamSynchronize(L.stream));
-  double m = 0.0;
-  for (double v : h) m = std::max(m, v);
-  L.bmax = m;
-  UFG_TRY(launch_sca_setup(L, 1.0));
-  UFG_HIP(hipStreamSynchronize(L.stream));
+  L.bmax = *L.bmax_host;
   L.lam_max_valid = 0;
   L.lam_max_sq_valid = 0;
   return UFG_OK;
@@ -317,7 +316,7 @@ int create_lattice_dim(int nx, int ntau, int dim, double tau, double g, int dtyp
   if (!rc) rc = upload_constants<float>(*L, L->f32, Ut, lam3);
   if (!rc && hipMemsetAsync(L->sigma, 0, sizeof(double) * L->N, L->stream) != hipSuccess)
     rc = UFG_EHIP;
-  if (!rc) rc = install_field(*L);
+  if (!rc) rc = install_field(*L, L->sigma);
   if (rc) {
     free_fields(*L);
     delete L;
@@ -347,9 +346,7 @@ int set_aux_field(ufg_lattice h, const double* sigma_dev) {
   Lattice* L = check_handle(h);
   UFG_CHECK(L != nullptr, "set_aux_field: NULL handle");
   UFG_CHECK(sigma_dev != nullptr, "set_aux_field: sigma is NULL");
-  UFG_HIP(hipMemcpyAsync(L->sigma, sigma_dev, sizeof(double) * L->N, hipMemcpyDeviceToDevice,
-                         L->stream));
-  return install_field(*L);
+  return install_field(*L, sigma_dev);
 }
 
 int apply_M(ufg_lattice h, const void* x, void* y, int nrhs) {

@@ -125,8 +125,7 @@ int solve_step(Md& m, int op, const void* b, void* x, bool guess) {
 // S_p and its gradient (into m.grad) at sigma; 1 when a solve failed.
 int force_at(Md& m, const double* sigma, double* S) {
   Lattice& L = m.L;
-  UFG_HIP(hipMemcpyAsync(L.sigma, sigma, sizeof(double) * L.N, hipMemcpyDeviceToDevice, L.stream));
-  UFG_TRY(install_field(L));
+  UFG_TRY(install_field(L, sigma));
   int rc = solve_step(m, UFG_OP_MDAG, m.phi, m.y, m.y_guess);
   if (rc) return rc;
   std::vector<double> nrm(m.nphi);
@@ -207,8 +206,7 @@ int restore(Lattice& L, double* sigma, double* pi) {
   const size_t fbytes = sizeof(double) * L.N;
   UFG_HIP(hipMemcpyAsync(sigma, L.hmc[HB_SIGMA0].p, fbytes, hipMemcpyDeviceToDevice, L.stream));
   UFG_HIP(hipMemcpyAsync(pi, L.hmc[HB_PI0].p, fbytes, hipMemcpyDeviceToDevice, L.stream));
-  UFG_HIP(hipMemcpyAsync(L.sigma, sigma, fbytes, hipMemcpyDeviceToDevice, L.stream));
-  return install_field(L);
+  return install_field(L, sigma);
 }
 
 int save_start(Lattice& L, const double* sigma, const double* pi) {
@@ -272,9 +270,7 @@ int hmc_trajectory(ufg_lattice h, const ufg_precond* precond, double* sigma_dev,
   UFG_CHECK(phi_out != eta_dev, "hmc_trajectory: phi_out must not alias eta");
   UFG_TRY(save_start(L, sigma_dev, pi_dev));
   // heat bath at the starting field
-  UFG_HIP(hipMemcpyAsync(L.sigma, sigma_dev, sizeof(double) * L.N, hipMemcpyDeviceToDevice,
-                         L.stream));
-  UFG_TRY(install_field(L));
+  UFG_TRY(install_field(L, sigma_dev));
   void* phi = L.hmc[HB_PHI].p;
   if (L.dtype == UFG_C128)
     UFG_TRY(op_apply<double>(L, UFG_OP_MDAG, (const double2*)eta_dev, (double2*)phi, nphi, nullptr));

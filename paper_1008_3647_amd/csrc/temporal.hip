@@ -13,13 +13,16 @@
 namespace ufg {
 namespace {
 
-__global__ void field_setup_kernel(const double* __restrict__ sigma, double A, long long n,
-                                   double* b64, double* s64, double* c64, float* b32, float* s32,
+// `sigma` is copied to `own` on the way (null: it is the library's copy already).
+__global__ void field_setup_kernel(const double* __restrict__ sigma, double* own, double A,
+                                   long long n, double* b64, double* s64, double* c64, float* b32, float* s32,
                                    float* c32, double* bmax_part) {
   double m = 0.0;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
        i += (long long)gridDim.x * blockDim.x) {
-    const double s = sin(sigma[i]), c = cos(sigma[i]);
+    const double sg = sigma[i];
+    if (own) own[i] = sg;
+    const double s = sin(sg), c = cos(sg);
     const double b = 1.0 + A * s;
     b64[i] = b;
     s64[i] = s;
@@ -44,29 +47,101 @@ __global__ void field_setup_kernel(const double* __restrict__ sigma, double A, l
 // D_0 = alpha + b_0^2; D_t = alpha + b_t^2 - b_{t-1}^2 / D_{t-1};
 // D_{Ntau-1} additionally loses b_{Ntau-1}^2 / D_0 (the antiperiodic corner);
 // L_t = b_t / D_t for t < Ntau-1 and L_{Ntau-1} = b_{Ntau-1} / D_0.
-__global__ void sca_setup_kernel(const double* __restrict__ b, int V, int ntau, double alpha,
-                                 double* D64, double* L64, float* D32, float* L32) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= V) return;
-  const double b0 = b[n];
-  const double D0 = alpha + b0 * b0;
-  double Dprev = D0, bprev = b0;
-  D64[n] = D0;
-  for (int t = 1; t < ntau; ++t) {
-    const long long i = (long long)t * V + n;
-    const double bt = b[i];
-    double D = alpha + bt * bt - bprev * bprev / Dprev;
-    if (t == ntau - 1) D -= bt * bt / D0;
-    D64[i] = D;
-    L64[i - V] = bprev / Dprev;
-    Dprev = D;
-    bprev = bt;
+// The chain of one FP64 division per slice (0.14 us each) is what bounds one
+// thread per site (12^3 x 200: 114 us with a load wait in every step, 28 us with
+// the loads ahead of the chain), so a site's time line is split into chunks.
+// With D_t = b_t^2 + E_t and q = b_{t-1}^2 a step is the projective map E -> (alpha
+// E + (alpha - 1) q) / (E + q), whose terms are all positive for alpha >= 1:
+// every chunk multiplies its 2 x 2 matrices (no division, no cancellation), the
+// products of the chunks before are applied to (E_0 = alpha, 1), and the
+// recursion as printed runs from there. Matrices and vectors are rescaled by
+// powers of two. Against long double over Ntau = 2..1000, alpha = 1..3: error
+// no larger than the recursion's from D_0 (alpha = 1, Ntau = 200: 4e-13 against
+// 4e-11, and equal where that is at rounding level).
+// The last workgroup instead writes the largest of the nblk partial maxima to
+// bmax_host (pinned host memory; none when null).
+constexpr int kSetupSites = 16, kSetupChunks = 32;
+__global__ void __launch_bounds__(kSetupSites* kSetupChunks)
+    sca_setup_kernel(const double* __restrict__ b, int V, int ntau, double alpha,
+                     double* __restrict__ D64, double* __restrict__ L64, float* __restrict__ D32,
+                     float* __restrict__ L32, const double* __restrict__ bmax_part, int nblk,
+                     double* bmax_host) {
+  __shared__ double sm[4][kSetupChunks][kSetupSites];
+  if (bmax_host && blockIdx.x == gridDim.x - 1) {
+    if (threadIdx.x >= 64) return;
+    double m = 0.0;
+    for (int i = threadIdx.x; i < nblk; i += 64) m = fmax(m, bmax_part[i]);
+    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+    if (threadIdx.x == 0) *bmax_host = m;
+    return;
   }
-  L64[(long long)(ntau - 1) * V + n] = bprev / D0;
-  for (int t = 0; t < ntau; ++t) {
+  const int ml = threadIdx.x % kSetupSites, c = threadIdx.x / kSetupSites;
+  const int n = blockIdx.x * kSetupSites + ml;
+  const bool act = n < V;
+  const int K = (ntau - 1 + kSetupChunks - 1) / kSetupChunks;  // steps t = 1 .. ntau - 1
+  const int s0 = min(1 + c * K, ntau), s1 = min(s0 + K, ntau);
+  auto bat = [&](int t) -> double { return b[(long long)t * V + n]; };
+  auto scale_of = [](double v) -> int { return max(-1000, min(1000, -ilogb(v))); };
+  double m00 = 1.0, m01 = 0.0, m10 = 0.0, m11 = 1.0, b0 = 0.0;
+  if (act) {
+    b0 = bat(0);
+#pragma unroll 8
+    for (int t = s0; t < s1; ++t) {
+      const double bp = bat(t - 1), q = bp * bp, f = (alpha - 1.0) * q;
+      const double u0 = alpha * m00 + f * m10, u1 = alpha * m01 + f * m11;
+      m10 = m00 + q * m10;
+      m11 = m01 + q * m11;
+      m00 = u0;
+      m01 = u1;
+      if (((t - s0) & 7) == 7) {
+        const int x = scale_of(fmax(fabs(m00), fabs(m01)));
+        m00 = ldexp(m00, x);
+        m01 = ldexp(m01, x);
+        m10 = ldexp(m10, x);
+        m11 = ldexp(m11, x);
+      }
+    }
+  }
+  sm[0][c][ml] = m00;
+  sm[1][c][ml] = m01;
+  sm[2][c][ml] = m10;
+  sm[3][c][ml] = m11;
+  __syncthreads();
+  if (!act) return;
+  const double D0 = alpha + b0 * b0;
+  double v0 = alpha, v1 = 1.0;
+  for (int j = 0; j < c; ++j) {
+    const double u0 = sm[0][j][ml] * v0 + sm[1][j][ml] * v1;
+    const double u1 = sm[2][j][ml] * v0 + sm[3][j][ml] * v1;
+    const int x = scale_of(u1);
+    v0 = ldexp(u0, x);
+    v1 = ldexp(u1, x);
+  }
+  if (c == 0) {
+    D64[n] = D0;
+    D32[n] = float(D0);
+  }
+  if (s0 >= s1) return;
+  double bp = bat(s0 - 1);
+  double Dp = c == 0 ? D0 : bp * bp + v0 / v1;
+#pragma unroll 8
+  for (int t = s0; t < s1; ++t) {
     const long long i = (long long)t * V + n;
-    D32[i] = float(D64[i]);
-    L32[i] = float(L64[i]);
+    const double bt = bat(t);
+    double D = alpha + bt * bt - bp * bp / Dp;
+    if (t == ntau - 1) D -= bt * bt / D0;
+    const double Lp = bp / Dp;
+    D64[i] = D;
+    D32[i] = float(D);
+    L64[i - V] = Lp;
+    L32[i - V] = float(Lp);
+    Dp = D;
+    bp = bt;
+  }
+  if (s1 == ntau) {
+    const double Ll = bp / D0;
+    L64[(long long)(ntau - 1) * V + n] = Ll;
+    L32[(long long)(ntau - 1) * V + n] = float(Ll);
   }
 }
 
@@ -324,18 +399,20 @@ __global__ void __launch_bounds__(kModes* kChunks)
 
 }  // namespace
 
-int launch_field_setup(Lattice& L, double* bmax_part, int nblk) {
-  hipLaunchKernelGGL(field_setup_kernel, dim3(nblk), dim3(256), 0, L.stream, L.sigma, L.A, L.N,
-                     L.f64.b, L.f64.sn, L.f64.cs, L.f32.b, L.f32.sn, L.f32.cs, bmax_part);
+int launch_field_setup(Lattice& L, const double* sigma, double* bmax_part, int nblk) {
+  hipLaunchKernelGGL(field_setup_kernel, dim3(nblk), dim3(256), 0, L.stream, sigma,
+                     sigma == L.sigma ? nullptr : L.sigma, L.A, L.N, L.f64.b, L.f64.sn, L.f64.cs,
+                     L.f32.b, L.f32.sn, L.f32.cs, bmax_part);
   UFG_HIP(hipGetLastError());
   return UFG_OK;
 }
 
-int launch_sca_setup(Lattice& L, double alpha) {
-  const int threads = 256;
-  hipLaunchKernelGGL(sca_setup_kernel, dim3((L.V + threads - 1) / threads), dim3(threads), 0,
+int launch_sca_setup(Lattice& L, double alpha, const double* bmax_part, int nblk,
+                     double* bmax_host) {
+  hipLaunchKernelGGL(sca_setup_kernel, dim3((L.V + kSetupSites - 1) / kSetupSites + (bmax_host ? 1 : 0)),
+                     dim3(kSetupSites * kSetupChunks), 0,
                      L.stream, L.f64.b, L.V, L.ntau, alpha, L.f64.scaD, L.f64.scaL, L.f32.scaD,
-                     L.f32.scaL);
+                     L.f32.scaL, bmax_part, nblk, bmax_host);
   UFG_HIP(hipGetLastError());
   L.sca_alpha = alpha;
   return UFG_OK;

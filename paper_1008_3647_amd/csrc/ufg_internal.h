@@ -94,6 +94,7 @@ struct Lattice {
   int device = 0;
   double* sigma = nullptr;  // FP64 copy of the field
   double bmax = 1.0;        // max |1 + A sin sigma|
+  double* bmax_host = nullptr;  // pinned; where the setup kernel leaves it
   double sca_alpha = 1.0;   // alpha the SCA blocks were built with
   Fields<double> f64;
   Fields<float> f32;
@@ -217,19 +218,23 @@ int launch_force(const Lattice& L, const C2<R>* X, const C2<R>* y, int nrhs, dou
 // Temporal kernels.
 template <typename R>
 int launch_sca_apply(const Lattice& L, const C2<R>* v, C2<R>* x, int nrhs, const int* gate);
-int launch_sca_setup(Lattice& L, double alpha);
+// With bmax_host (pinned), also the largest of the nblk partial maxima.
+int launch_sca_setup(Lattice& L, double alpha, const double* bmax_part = nullptr, int nblk = 0,
+                     double* bmax_host = nullptr);
 // (1 - lam Z)^{-1} v per spatial mode (adjoint: Z^T); subtract_input: result - v.
 // scale_field (may be null, indexed by t, n) multiplies the result.
 template <typename R>
 int launch_m0_temporal(const Lattice& L, const C2<R>* v, C2<R>* u, int nrhs, bool adjoint,
                        bool subtract_input, const int* gate);
 
-// Field setup: b, sin, cos from sigma in both precisions; per-block max |b| into bmax_part.
-int launch_field_setup(Lattice& L, double* bmax_part, int nblk);
+// Field setup: the library's copy of sigma (unless sigma is it), and b, sin, cos
+// from it in both precisions; per-block max |b| into bmax_part.
+int launch_field_setup(Lattice& L, const double* sigma, double* bmax_part, int nblk);
 
-// Everything derived from L.sigma (both precisions, max |b|, SCA blocks);
-// synchronizes the lattice stream.
-int install_field(Lattice& L);
+// Installs sigma (device; may be L.sigma): the library's copy and everything
+// derived from it (both precisions, max |b|, SCA blocks); synchronizes the
+// lattice stream.
+int install_field(Lattice& L, const double* sigma);
 // out_host[r] = ||x_r||^2 (FP64, fixed order) for nrhs vectors of the lattice
 // dtype; synchronous.
 int norm2_host(Lattice& L, const void* x, int nrhs, double* out_host);

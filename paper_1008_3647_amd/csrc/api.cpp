@@ -145,8 +145,8 @@ static void free_fields(Lattice& L) {
   if (L.bmax_host) (void)hipHostFree(L.bmax_host);
 }
 
-// The constants of one precision (T, U, U^T, mode eigenvalues, block forms of U^T
-// and U where they exist) in one allocation, owned through F.T, and one copy.
+// The constants of one precision (T, U, U^T, mode eigenvalues, block forms of T,
+// U^T and U where they exist) in one allocation, owned through F.T, and one copy.
 template <typename R>
 static int upload_constants(Lattice& L, Fields<R>& F, const std::vector<double>& Ut,
                             const std::vector<double>& lam) {
@@ -159,7 +159,8 @@ static int upload_constants(Lattice& L, Fields<R>& F, const std::vector<double>&
   };
   std::vector<double> modes = L.mode_fwd_host;
   modes.insert(modes.end(), L.mode_bwd_host.begin(), L.mode_bwd_host.end());
-  const size_t t = put(L.T_host), u = put(L.U_host), ut = put(Ut), la = put(lam), mo = put(modes);
+  const size_t t = put(L.T_host), u = put(L.U_host), ut = put(Ut), la = put(lam), mo = put(modes),
+               sp = put(L.split_host);
   R* base = nullptr;
   if (hipMalloc(&base, h.size() * sizeof(R)) != hipSuccess) {
     (void)hipGetLastError();
@@ -171,6 +172,7 @@ static int upload_constants(Lattice& L, Fields<R>& F, const std::vector<double>&
   F.Ut = base + ut;
   F.lam = base + la;
   F.modes = modes.empty() ? nullptr : base + mo;
+  F.split = L.split_host.empty() ? nullptr : base + sp;
   UFG_HIP(hipMemcpyAsync(base, h.data(), h.size() * sizeof(R), hipMemcpyHostToDevice, L.stream));
   UFG_HIP(hipStreamSynchronize(L.stream));
   return UFG_OK;

@@ -40,4 +40,10 @@ bool stream_supported(const Lattice& L);
 template <typename R>
 int launch_hop_stream(const Lattice& L, const HopArgs<R>& a);
 
+// y = alpha Q x + beta x, Q = M^T M, in one launch (hop_q.hip; stream_supported
+// lattices). y must not alias x.
+template <typename R>
+int launch_hop_q(const Lattice& L, const C2<R>* x, C2<R>* y, double2 alpha, double2 beta, int nrhs,
+                 const int* gate);
+
 }  // namespace ufg

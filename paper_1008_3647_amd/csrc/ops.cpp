@@ -13,6 +13,7 @@
 //     so every order of the expansion costs two spatial basis changes and one
 //     temporal sweep, with the M1 factor folded into them.
 #include "ops.h"
+#include "hop_stream.h"
 #include "wce.h"
 
 #include <cmath>
@@ -358,17 +359,32 @@ static int cheb_apply(Lattice& L, const PcPlan& pc, const C2<R>* x, C2<R>* y, in
   UFG_TRY(rc);
   const std::complex<double> cf(pc.cf.x, pc.cf.y);
   const C2<R>* cur = x;
-  for (size_t i = 0; i < pc.roots.size(); ++i) {
+  const size_t n = pc.roots.size();
+  auto factor = [&](size_t i, double2* alpha, double2* beta) {
     const std::complex<double> z(pc.roots[i].x, pc.roots[i].y);
     const std::complex<double> al = cf / pc.lam_max, be = -cf * z;
+    *alpha = double2{al.real(), al.imag()};
+    *beta = double2{be.real(), be.imag()};
+  };
+  const bool one_launch = stream_supported(L);
+  for (size_t i = 0; i < n; ++i) {
+    double2 alpha, beta;
+    factor(i, &alpha, &beta);
+    cnt->mv += 2;
+    if (one_launch) {  // the factors alternate between tmp and y, the last one in y
+      C2<R>* out = (n - 1 - i) % 2 == 0 ? y : tmp;
+      UFG_TRY(launch_hop_q<R>(L, cur, out, alpha, beta, nrhs, gate));
+      cur = out;
+      continue;
+    }
     UFG_TRY(op_apply<R>(L, UFG_OP_M, cur, tmp, nrhs, gate));
     HopArgs<R> a;
     a.src = tmp;
     a.id = tmp;
     a.dst = y;
     a.aux = cur;
-    a.alpha = double2{al.real(), al.imag()};
-    a.beta = double2{be.real(), be.imag()};
+    a.alpha = alpha;
+    a.beta = beta;
     a.mat = F.T;
     a.shift = kShiftMdag;
     a.post = F.b;
@@ -376,7 +392,6 @@ static int cheb_apply(Lattice& L, const PcPlan& pc, const C2<R>* x, C2<R>* y, in
     a.gate = gate;
     UFG_TRY(launch_hop<R>(L, a));
     cur = y;
-    cnt->mv += 2;
   }
   return UFG_OK;
 }

@@ -68,13 +68,29 @@ __device__ __forceinline__ void line_op(const CoefPtr<R, NX>& c, El (&v)[NX]) {
   line_op<MODE, R, NX>(*q, v);
 }
 
+// Ordering point inside one wave: LDS operations of a wave are performed in
+// order; the fences keep the compiler from moving reads above writes.
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// Barrier among the threads of one slice: the slice of Nx = 8 is one wave.
+template <int NX>
+__device__ __forceinline__ void slice_sync() {
+  if constexpr (NX * NX == 64)
+    wave_order();
+  else
+    __syncthreads();
+}
+
 template <typename R, int NX, int MODE = 0, bool KEEP = false, typename Coef, typename El>
 __device__ __forceinline__ void slice_T3(const Coef& c, El* lds, int l, El (&v)[NX]) {
   const int y = l / NX, x = l - (l / NX) * NX;
   line_op<MODE, R, NX>(c, v);  // along z
 #pragma unroll
   for (int z = 0; z < NX; ++z) lds[lds_at<NX>(z * NX + y, x)] = v[z];
-  __syncthreads();
+  slice_sync<NX>();
   El w[NX];
   {
     const int z = l / NX, xx = l - (l / NX) * NX;
@@ -85,11 +101,7 @@ __device__ __forceinline__ void slice_T3(const Coef& c, El* lds, int l, El (&v)[
     for (int yy = 0; yy < NX; ++yy) lds[lds_at<NX>(z * NX + yy, xx)] = w[yy];
   }
   if constexpr (64 % NX == 0) {
-    // LDS operations of one wave are performed in order; the fences keep the
-    // compiler from moving the reads above the writes
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_order();
   } else {
     __syncthreads();
   }
@@ -101,7 +113,7 @@ __device__ __forceinline__ void slice_T3(const Coef& c, El* lds, int l, El (&v)[
 #pragma unroll
     for (int xx = 0; xx < NX; ++xx) lds[lds_at<NX>(z * NX + yy, xx)] = w[xx];
   }
-  __syncthreads();
+  slice_sync<NX>();
   if (KEEP) return;  // the result stays in LDS: z-line of thread (y, x) at lds_at(z NX + y, x)
 #pragma unroll
   for (int z = 0; z < NX; ++z) v[z] = lds[lds_at<NX>(z * NX + y, x)];

@@ -60,6 +60,7 @@ struct Fields {
   R* U = nullptr;       // eigenvectors of T (columns)     [nx*nx]
   R* Ut = nullptr;      // U^T                             [nx*nx]
   R* lam = nullptr;     // eigenvalue of U^3 mode n        [V]
+  R* split = nullptr;   // block form of T                 (SplitCoef; null without it)
   R* modes = nullptr;   // block forms of U^T, then U      (SplitCoef each; null without them)
 };
 

@@ -109,7 +109,7 @@ typedef struct {
  *              there), so a solve ends up to two intervals after convergence
  *              on launches that do no work (not counted in the statistics).
  *   eager      0: where the iteration is not fused into the streaming kernel
- *              (preconditioned solves, CG, Nx outside {8, 12, 16}), every
+ *              (preconditioned solves, CG, Nx = 2 and 4), every
  *              check interval after the first replays a HIP graph captured
  *              from the same launches (same results; fewer host launches for
  *              small lattices). 1: launch every kernel separately.
@@ -406,7 +406,7 @@ int lattice_norm2_noalloc(ufg_lattice L, const void* x, int nrhs, double* out_de
 /*
  * lattice_tune -- launch parameters chosen by the autotuner (0 keeps the
  *   default): `slab` time slices per workgroup of the streaming M / M^T kernel
- *   (Nx in {8, 12, 16}; 1..Ntau), `vec_blocks` workgroups per right-hand side of
+ *   (Nx = 6 to 16; 1..Ntau), `vec_blocks` workgroups per right-hand side of
  *   the Krylov vector kernels (1..4096). Results do not depend on them beyond
  *   floating-point summation order.
  */

@@ -115,7 +115,7 @@ __device__ void bsum4b(double a0, double a1, double a2, double a3, double* out, 
 // segment, and each sub-group walks its slab like the single-lattice streaming
 // kernel (M upwards, M^T downwards): the slice loaded for the identity term of
 // one output is the source of the next, so only one halo slice per slab is
-// loaded twice. Nx in {8, 12, 16} use the reflection-symmetry block form of T;
+// loaded twice. Nx of 6 and more use the reflection-symmetry block form of T;
 // the other Nx apply T as a dense Nx x Nx matrix.
 
 __host__ __device__ constexpr int bop_groups(int nx) {
@@ -124,7 +124,7 @@ __host__ __device__ constexpr int bop_groups(int nx) {
 __host__ __device__ constexpr int bop_threads(int nx) {
   return ((bop_groups(nx) * nx * nx + 63) / 64) * 64;
 }
-__host__ __device__ constexpr bool bop_split(int nx) { return nx == 8 || nx == 12 || nx == 16; }
+__host__ __device__ constexpr bool bop_split(int nx) { return nx >= 6; }
 
 template <typename R, int NX, bool SPLIT>
 struct BCoef;
@@ -563,7 +563,7 @@ struct Dev {
 // Operator class: segments with the same Nx and T share one launch.
 struct BClass {
   int nx = 0;
-  std::vector<double> T, coef;  // coef: block form (Nx in {8, 12, 16}) or T
+  std::vector<double> T, coef;  // coef: block form (Nx of 6 and more) or T
   int i0 = 0, i1 = 0;           // item range in the operator table (host copy)
   int nmax = 0;                 // items of the class with every segment live
   const int* range = nullptr;   // device copy of {i0, i1}

@@ -1,4 +1,5 @@
-// Slice operator kernels for gfx950.
+// General slice operator kernels for gfx950 (Nx = 2 and 4, lattices beyond the
+// streaming kernel's 32-bit offsets, and the general form of the basis changes).
 //
 // Every application of M, M^T, M1, M1^T (paper, Sec. 1 Eq. MatrixM and Sec. 3
 // Eq. MatrixM_1) and every change of spatial basis used by M0^{-1} is the same

@@ -147,6 +147,13 @@ int launch_q(const Lattice& L, const QArgs<R>& a) {
 
 }  // namespace
 
+bool hop_q_pays(const Lattice& L, int nrhs, bool fp64) {
+  // complex128 slices of Nx = 14 (47 KB of LDS each, two of them leave one
+  // workgroup per CU): two launches once the chip is full (degree 8 on 14^3 x
+  // 400, 8 rhs 1164 us against 1267 us; 14^3 x 100, 1 rhs 104 us fused)
+  return stream_supported(L) && !(fp64 && L.nx == 14 && (long long)L.ntau * nrhs > 512);
+}
+
 template <typename R>
 int launch_hop_q(const Lattice& L, const C2<R>* x, C2<R>* y, double2 alpha, double2 beta, int nrhs,
                  const int* gate) {
@@ -160,12 +167,19 @@ int launch_hop_q(const Lattice& L, const C2<R>* x, C2<R>* y, double2 alpha, doub
   // 8^3 x 160, 4 rhs complex128 130 / - / 98 / 119 (6), 8^3 x 400, 8 rhs 243 / - / 255 / 241
   // (8); 12^3 x 200, 1 rhs complex128 157 / 182 / 250 / 268, 8 rhs 896 / 722 / 842 / 647;
   // 16^3 x 400, 8 rhs complex64 1184 / 1423 / 1324 / - (complex128: two slices fill the
-  // LDS). In two launches a factor (M, then M^T with the scaling): 168, 437, 213, 776,
+  // LDS); degree 8, 10^3 x 200, 1 rhs complex128 61 / 67 / 77 / 90 (6), 10^3 x 400, 8 rhs 338 /
+  // 410 / 381 / 316 (6). In two launches a factor (M, then M^T with the scaling): 168, 437, 213, 776,
   // 1670 us, and complex128 16^3 x 400, 8 rhs 3492 -> 2960 us.
   const long long n = (long long)L.ntau * nrhs;  // slices
   switch (L.nx) {
+    case 6: return n < 2048 ? launch_q<R, 6, 4>(L, a) : launch_q<R, 6, 8>(L, a);
     case 8: return n < 2048 ? launch_q<R, 8, 4>(L, a) : launch_q<R, 8, 8>(L, a);
+    case 10:
+      return n <= 512 ? launch_q<R, 10, 2>(L, a) : launch_q<R, 10, sizeof(R) == 4 ? 5 : 6>(L, a);
     case 12: return n <= 512 ? launch_q<R, 12, 2>(L, a) : launch_q<R, 12, 5>(L, a);
+    case 14:
+      if (sizeof(R) == 4 && n > 1024) return launch_q<R, 14, 4>(L, a);
+      return launch_q<R, 14, 2>(L, a);
     case 16: return launch_q<R, 16, 2>(L, a);
     default: set_error("fused M^T M: unsupported nx"); return UFG_EINVAL;
   }

@@ -21,8 +21,8 @@
 // exp(-tau K) along one axis is the symmetric circulant T. T commutes with the
 // reflections i -> -i and i -> Nx/2 - i (mod Nx), so in the basis of their
 // joint eigenvectors (built by two levels of add/subtract butterflies) T is
-// block diagonal with blocks of sizes Nx/4+1, Nx/4, Nx/4, Nx/4-1. A line of Nx
-// values then costs 4 (Nx-2) additions for the butterflies and sum(block^2)
+// block diagonal with four blocks of about Nx/4 (SplitSize). A line of Nx values
+// then costs about 4 Nx additions for the butterflies and sum(block^2)
 // multiply-adds (56 + 66 for Nx = 16) instead of Nx^2 = 256 multiply-adds.
 //
 // Memory access: raw buffer instructions with one resource per array (base =
@@ -345,11 +345,12 @@ __global__ void __launch_bounds__(NX * NX)
   // every complex64 variant and the fused complex128 ones, slower for the
   // plain complex128 operator, which keeps the default policy).
   constexpr int kNTA = (sizeof(R) == 4 || SRC != 0 || RED != 0) ? kAuxNT : 0;
-  // plain complex64 operator: the first output slice's source (and, for M^T,
-  // its field) is loaded together with the halo, before the halo's transform
-  // (one more z-line of registers; the fused variants would lose a wave per
-  // SIMD to it)
-  constexpr bool EARLY = sizeof(R) == 4 && SRC == 0 && RED == 0 && !GENERAL;
+  // plain operator: the first output slice's source (and, for M^T, its field) is
+  // loaded together with the halo, before the halo's transform (one more z-line
+  // of registers; the fused variants would lose a wave per SIMD to it).
+  // complex128 up to Nx = 10, M^T also at Nx = 12: 8^3 x 400, 8 rhs 10.2 / 10.7 (M / M^T)
+  // -> 9.7 / 9.6 us, 12^3 x 400, 8 rhs M^T 41.9 -> 40.2 but M 41.5 -> 43.6.
+  constexpr bool EARLY = (sizeof(R) == 4 || NX <= 10 || (NX == 12 && DIR > 0)) && SRC == 0 && RED == 0 && !GENERAL;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   C2<R>* lds = reinterpret_cast<C2<R>*>(smem_raw);
 
@@ -481,7 +482,7 @@ __global__ void __launch_bounds__(NX * NX)
   // workgroups started earlier finish (and free their slots) first (measured:
   // apply_Mdag 45.9 -> 43.6 us, apply_M unchanged; the fused and complex128
   // variants ran slower that way)
-  if constexpr (EARLY) __builtin_amdgcn_s_setprio(2);
+  if constexpr (EARLY && sizeof(R) == 4) __builtin_amdgcn_s_setprio(2);
   if (DIR < 0) scale_field<R, NX>(b.pre, th * V * FS, fo, X);
   if constexpr (TR == 1)
     slice_T3_mfma16(cc, ta, lds, l, X);
@@ -768,8 +769,13 @@ int stream_grid(const Lattice& L, int nrhs) {
 bool stream_supported(const Lattice& L) {
   // buffer offsets are 32-bit: one rhs block of complex128 must stay below 2 GiB
   const long long block = (long long)L.ntau * L.nx * L.nx * L.nx * (long long)sizeof(double2);
-  return (L.nx == 8 || L.nx == 12 || L.nx == 16) && !L.split_host.empty() &&
-         block < (1ll << 31);
+  // Every Nx with a block form (6 to 16). Nx = 6, 10 and 14 ran in the general slice
+  // kernel before (dense lines, every slice loaded twice), M / M^T us: 10^3 x 201, 3
+  // rhs complex128 13.3 / 15.1 -> 6.7 / 7.1, 10^3 x 400, 8 rhs complex64 20.4 / 22.7 -> 11.2 /
+  // 11.1, 14^3 x 400, 8 rhs complex128 100 / 108 -> 64 / 64, 6^3 x 800, 64 rhs complex64
+  // 46.6 / 50.8 -> 42.9 / 43.1 (36 of a wave's 64 lanes hold a line there), 6^3 x 50
+  // complex128 6.5 / 6.7 -> 6.2 / 6.3. Nx = 2 and 4 keep it: several slices to a wave.
+  return !L.split_host.empty() && block < (1ll << 31);
 }
 
 template <typename R>
@@ -790,7 +796,10 @@ int launch_hop_stream(const Lattice& L, const HopArgs<R>& args) {
     return UFG_EINVAL;
   }
   switch (L.nx) {
+    case 6: return launch_nx<R, 6>(L, a);
     case 8: return launch_nx<R, 8>(L, a);
+    case 10: return launch_nx<R, 10>(L, a);
+    case 14: return launch_nx<R, 14>(L, a);
     case 12: return launch_nx<R, 12>(L, a);
     case 16: return launch_nx<R, 16>(L, a);
     default: set_error("streaming kernel: unsupported nx"); return UFG_EINVAL;

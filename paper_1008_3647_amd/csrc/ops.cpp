@@ -366,7 +366,7 @@ static int cheb_apply(Lattice& L, const PcPlan& pc, const C2<R>* x, C2<R>* y, in
     *alpha = double2{al.real(), al.imag()};
     *beta = double2{be.real(), be.imag()};
   };
-  const bool one_launch = stream_supported(L);
+  const bool one_launch = hop_q_pays(L, nrhs, sizeof(R) == 8);
   for (size_t i = 0; i < n; ++i) {
     double2 alpha, beta;
     factor(i, &alpha, &beta);

@@ -3,6 +3,7 @@
 // add/subtract butterfly and y = P' v its inverse written with additions only,
 // B = P'^{-1} T P^{-1} is block diagonal (reflection symmetries of T); the
 // blocks are returned in the order the kernel consumes them.
+#include <algorithm>
 #include <cmath>
 
 #include "hop_stream.h"
@@ -39,10 +40,28 @@ static bool invert(int n, std::vector<double> a, std::vector<double>* inv) {
   return true;
 }
 
+// Block sizes as SplitSize (hop_stream.h).
+struct BlockSizes {
+  int es, ea, os, oa;
+  explicit BlockSizes(int nx) {
+    const int H = nx / 2;
+    if (H % 2 == 0) {
+      es = H / 2 + 1;
+      ea = os = H / 2;
+      oa = H / 2 - 1;
+    } else {
+      es = ea = (H + 1) / 2;
+      os = oa = (H - 1) / 2;
+    }
+  }
+};
+static bool has_blocks(int nx) { return nx % 2 == 0 && nx >= 6; }
+
 // P: positions -> reflection-symmetry components (block order es, ea, os,
 // oa); Pp: the inverse written with additions only (as the kernels do).
 static void butterfly_matrices(int nx, std::vector<double>* Pout, std::vector<double>* Ppout) {
-  const int n = nx, H = nx / 2, Q = nx / 4;
+  const int n = nx, H = nx / 2;
+  const BlockSizes z(nx);
   // rows of P: E_j = x_j + x_{-j} (x_0, x_H alone), O_j = x_j - x_{-j}
   auto Erow = [&](int j) {
     std::vector<double> v(n, 0.0);
@@ -56,61 +75,46 @@ static void butterfly_matrices(int nx, std::vector<double>* Pout, std::vector<do
     v[n - j] -= 1.0;
     return v;
   };
+  // S and A rows: sum and difference of the pair (j, H - j); the fixed point
+  // j = H / 2 (H even) is a row of its own behind the S rows
   std::vector<std::vector<double>> rows;
-  for (int j = 0; j < Q; ++j) {  // ES_j = E_j + E_{H-j}
-    auto a = Erow(j), b = Erow(H - j);
-    for (int k = 0; k < n; ++k) a[k] += b[k];
-    rows.push_back(a);
-  }
-  rows.push_back(Erow(Q));
-  for (int j = 0; j < Q; ++j) {  // EA_j = E_j - E_{H-j}
-    auto a = Erow(j), b = Erow(H - j);
-    for (int k = 0; k < n; ++k) a[k] -= b[k];
-    rows.push_back(a);
-  }
-  for (int j = 1; j < Q; ++j) {  // OS_j = O_j + O_{H-j}
-    auto a = Orow(j), b = Orow(H - j);
-    for (int k = 0; k < n; ++k) a[k] += b[k];
-    rows.push_back(a);
-  }
-  rows.push_back(Orow(Q));
-  for (int j = 1; j < Q; ++j) {  // OA_j = O_j - O_{H-j}
-    auto a = Orow(j), b = Orow(H - j);
-    for (int k = 0; k < n; ++k) a[k] -= b[k];
-    rows.push_back(a);
-  }
+  auto pair_rows = [&](auto row, int first, int count, double sign) {
+    for (int j = first; j < first + count; ++j) {
+      auto a = row(j), b = row(H - j);
+      for (int k = 0; k < n; ++k) a[k] += sign * b[k];
+      rows.push_back(a);
+    }
+  };
+  pair_rows(Erow, 0, z.ea, 1.0);
+  if (H % 2 == 0) rows.push_back(Erow(H / 2));
+  pair_rows(Erow, 0, z.ea, -1.0);
+  pair_rows(Orow, 1, z.oa, 1.0);
+  if (H % 2 == 0) rows.push_back(Orow(H / 2));
+  pair_rows(Orow, 1, z.oa, -1.0);
   std::vector<double> P(n * n), Pp(n * n, 0.0);
   for (int i = 0; i < n; ++i)
     for (int k = 0; k < n; ++k) P[i * n + k] = rows[i][k];
   // P': v = (ES', EA', OS', OA') -> y with additions only
-  const int nES = Q + 1, nEA = Q, nOS = Q;
-  auto iES = [&](int j) { return j; };
-  auto iEA = [&](int j) { return nES + j; };
-  auto iOS = [&](int j) { return nES + nEA + (j - 1); };
-  auto iOA = [&](int j) { return nES + nEA + nOS + (j - 1); };
+  const int oES = 0, oEA = z.es, oOS = z.es + z.ea, oOA = z.es + z.ea + z.os;
   auto Ep = [&](int j) {
     std::vector<double> v(n, 0.0);
-    if (j < Q) {
-      v[iES(j)] += 1;
-      v[iEA(j)] += 1;
-    } else if (j == Q) {
-      v[iES(Q)] += 1;
+    if (2 * j == H) {
+      v[oES + j] += 1;
     } else {
-      v[iES(H - j)] += 1;
-      v[iEA(H - j)] -= 1;
+      const int k = std::min(j, H - j);
+      v[oES + k] += 1;
+      v[oEA + k] += j == k ? 1 : -1;
     }
     return v;
   };
   auto Op = [&](int j) {
     std::vector<double> v(n, 0.0);
-    if (j < Q) {
-      v[iOS(j)] += 1;
-      v[iOA(j)] += 1;
-    } else if (j == Q) {
-      v[iOS(Q)] += 1;
+    if (2 * j == H) {
+      v[oOS + j - 1] += 1;
     } else {
-      v[iOS(H - j)] += 1;
-      v[iOA(H - j)] -= 1;
+      const int k = std::min(j, H - j);
+      v[oOS + k - 1] += 1;
+      v[oOA + k - 1] += j == k ? 1 : -1;
     }
     return v;
   };
@@ -135,8 +139,9 @@ static void butterfly_matrices(int nx, std::vector<double>* Pout, std::vector<do
 
 double split_coefficients(int nx, const std::vector<double>& T, std::vector<double>* out) {
   out->clear();
-  if (nx % 4 != 0 || nx < 8) return 0.0;
-  const int n = nx, Q = nx / 4;
+  if (!has_blocks(nx)) return 0.0;
+  const int n = nx;
+  const BlockSizes z(nx);
   std::vector<double> P, Pp;
   butterfly_matrices(nx, &P, &Pp);
   std::vector<double> Pi, Ppi;
@@ -154,7 +159,7 @@ double split_coefficients(int nx, const std::vector<double>& T, std::vector<doub
       for (int k = 0; k < n; ++k) s += Ppi[i * n + k] * tmp[k * n + j];
       B[i * n + j] = s;
     }
-  const int sizes[4] = {Q + 1, Q, Q, Q - 1};
+  const int sizes[4] = {z.es, z.ea, z.os, z.oa};
   int starts[4];
   starts[0] = 0;
   for (int b = 1; b < 4; ++b) starts[b] = starts[b - 1] + sizes[b - 1];
@@ -186,13 +191,14 @@ double mode_split_coefficients(int nx, const std::vector<double>& U, std::vector
   fwd->clear();
   bwd->clear();
   perm->clear();
-  if (nx % 4 != 0 || nx < 8) return 0.0;
-  const int n = nx, Q = nx / 4;
+  if (!has_blocks(nx)) return 0.0;
+  const int n = nx;
+  const BlockSizes z(nx);
   std::vector<double> P, Pp, Pi, Ppi;
   butterfly_matrices(nx, &P, &Pp);
   if (!invert(n, P, &Pi) || !invert(n, Pp, &Ppi)) return 1.0;
-  const int sizes[4] = {Q + 1, Q, Q, Q - 1};
-  const int starts[4] = {0, Q + 1, 2 * Q + 1, 3 * Q + 1};
+  const int sizes[4] = {z.es, z.ea, z.os, z.oa};
+  const int starts[4] = {0, z.es, z.es + z.ea, z.es + z.ea + z.os};
   auto block_of = [&](int j) {
     int b = 0;
     while (b < 3 && j >= starts[b + 1]) ++b;

@@ -37,18 +37,19 @@ __device__ __forceinline__ El zero_of() {
 }
 
 // y = T a for one line held in registers (in place), through the butterflies.
-// The four blocks of a line in the reflection-symmetry basis (Q = NX/4):
-// es[0..Q], ea[0..Q-1], os[1..Q], oa[1..Q-1].
+// The four blocks of a line in the reflection-symmetry basis (os and oa start
+// with index 1 of the line).
 template <typename El, int NX>
 struct Parts {
-  static constexpr int Q = NX / 4;
-  El es[Q + 1], ea[Q + 1], os[Q + 1], oa[Q + 1];
+  using Z = SplitSize<NX>;
+  El es[Z::ES], ea[Z::EA], os[Z::OS], oa[Z::OA];
 };
 
 // positions -> reflection-symmetry components (two butterfly levels)
 template <typename R, int NX, typename El>
 __device__ __forceinline__ void butterflies(const El (&a)[NX], Parts<El, NX>& p) {
-  constexpr int H = NX / 2, Q = NX / 4;
+  using Z = SplitSize<NX>;
+  constexpr int H = NX / 2;
   El E[H + 1], O[H + 1];
   E[0] = a[0];
   E[H] = a[H];
@@ -58,83 +59,64 @@ __device__ __forceinline__ void butterflies(const El (&a)[NX], Parts<El, NX>& p)
     O[j] = sub(a[j], a[NX - j]);
   }
 #pragma unroll
-  for (int j = 0; j < Q; ++j) {
+  for (int j = 0; j < Z::EA; ++j) {
     p.es[j] = add(E[j], E[H - j]);
     p.ea[j] = sub(E[j], E[H - j]);
   }
-  p.es[Q] = E[Q];
 #pragma unroll
-  for (int j = 1; j < Q; ++j) {
-    p.os[j] = add(O[j], O[H - j]);
-    p.oa[j] = sub(O[j], O[H - j]);
+  for (int j = 1; j <= Z::OA; ++j) {
+    p.os[j - 1] = add(O[j], O[H - j]);
+    p.oa[j - 1] = sub(O[j], O[H - j]);
   }
-  p.os[Q] = O[Q];
+  if constexpr (!Z::odd) {  // the fixed point of i -> NX/2 - i
+    p.es[H / 2] = E[H / 2];
+    p.os[H / 2 - 1] = O[H / 2];
+  }
+}
+
+// out = m in for one N x N block
+template <int N, typename M, typename El>
+__device__ __forceinline__ void one_block(const M& m, const El (&in)[N], El (&out)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    El s = zero_of<El>();
+#pragma unroll
+    for (int k = 0; k < N; ++k) s = madd(m[i * N + k], in[k], s);
+    out[i] = s;
+  }
 }
 
 // out = blockdiag(c) in, block by block
 template <typename R, int NX, typename Coef, typename El>
 __device__ __forceinline__ void blockmul(const Coef& c, const Parts<El, NX>& in,
                                          Parts<El, NX>& out) {
-  constexpr int Q = NX / 4;
-#pragma unroll
-  for (int i = 0; i <= Q; ++i) {
-    El s = zero_of<El>();
-#pragma unroll
-    for (int k = 0; k <= Q; ++k) {
-      const R m = c.es[i * (Q + 1) + k];
-      s = madd(m, in.es[k], s);
-    }
-    out.es[i] = s;
-  }
-#pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    El s = zero_of<El>();
-#pragma unroll
-    for (int k = 0; k < Q; ++k) {
-      const R m = c.ea[i * Q + k];
-      s = madd(m, in.ea[k], s);
-    }
-    out.ea[i] = s;
-  }
-#pragma unroll
-  for (int i = 1; i <= Q; ++i) {
-    El s = zero_of<El>();
-#pragma unroll
-    for (int k = 1; k <= Q; ++k) {
-      const R m = c.os[(i - 1) * Q + (k - 1)];
-      s = madd(m, in.os[k], s);
-    }
-    out.os[i] = s;
-  }
-#pragma unroll
-  for (int i = 1; i < Q; ++i) {
-    El s = zero_of<El>();
-#pragma unroll
-    for (int k = 1; k < Q; ++k) {
-      const R m = c.oa[(i - 1) * (Q - 1) + (k - 1)];
-      s = madd(m, in.oa[k], s);
-    }
-    out.oa[i] = s;
-  }
+  using Z = SplitSize<NX>;
+  one_block<Z::ES>(c.es, in.es, out.es);
+  one_block<Z::EA>(c.ea, in.ea, out.ea);
+  one_block<Z::OS>(c.os, in.os, out.os);
+  one_block<Z::OA>(c.oa, in.oa, out.oa);
 }
 
 // reflection-symmetry components -> positions (additions only)
 template <typename R, int NX, typename El>
 __device__ __forceinline__ void unbutterflies(const Parts<El, NX>& p, El (&a)[NX]) {
-  constexpr int H = NX / 2, Q = NX / 4;
+  using Z = SplitSize<NX>;
+  constexpr int H = NX / 2;
   El E[H + 1], O[H + 1];
 #pragma unroll
-  for (int j = 0; j < Q; ++j) {
+  for (int j = 0; j < Z::EA; ++j) {
     E[j] = add(p.es[j], p.ea[j]);
     E[H - j] = sub(p.es[j], p.ea[j]);
   }
-  E[Q] = p.es[Q];
 #pragma unroll
-  for (int j = 1; j < Q; ++j) {
-    O[j] = add(p.os[j], p.oa[j]);
-    O[H - j] = sub(p.os[j], p.oa[j]);
+  for (int j = 1; j <= Z::OA; ++j) {
+    O[j] = add(p.os[j - 1], p.oa[j - 1]);
+    O[H - j] = sub(p.os[j - 1], p.oa[j - 1]);
   }
-  O[Q] = p.os[Q];
+  if constexpr (!Z::odd) {
+    E[H / 2] = p.es[H / 2];
+    O[H / 2] = p.os[H / 2 - 1];
+  }
   a[0] = E[0];
   a[H] = E[H];
 #pragma unroll
@@ -156,27 +138,27 @@ __device__ __forceinline__ void split_line(const Coef& c, El (&a)[NX]) {
 // Mode-space packing of a line: the blocks in the order es, ea, os, oa.
 template <typename R, int NX, typename El>
 __device__ __forceinline__ void pack_modes(const Parts<El, NX>& p, El (&a)[NX]) {
-  constexpr int Q = NX / 4;
+  using Z = SplitSize<NX>;
 #pragma unroll
-  for (int j = 0; j <= Q; ++j) a[j] = p.es[j];
+  for (int j = 0; j < Z::ES; ++j) a[j] = p.es[j];
 #pragma unroll
-  for (int j = 0; j < Q; ++j) a[Q + 1 + j] = p.ea[j];
+  for (int j = 0; j < Z::EA; ++j) a[Z::ES + j] = p.ea[j];
 #pragma unroll
-  for (int j = 1; j <= Q; ++j) a[2 * Q + j] = p.os[j];
+  for (int j = 0; j < Z::OS; ++j) a[Z::ES + Z::EA + j] = p.os[j];
 #pragma unroll
-  for (int j = 1; j < Q; ++j) a[3 * Q + j] = p.oa[j];
+  for (int j = 0; j < Z::OA; ++j) a[Z::ES + Z::EA + Z::OS + j] = p.oa[j];
 }
 template <typename R, int NX, typename El>
 __device__ __forceinline__ void unpack_modes(const El (&a)[NX], Parts<El, NX>& p) {
-  constexpr int Q = NX / 4;
+  using Z = SplitSize<NX>;
 #pragma unroll
-  for (int j = 0; j <= Q; ++j) p.es[j] = a[j];
+  for (int j = 0; j < Z::ES; ++j) p.es[j] = a[j];
 #pragma unroll
-  for (int j = 0; j < Q; ++j) p.ea[j] = a[Q + 1 + j];
+  for (int j = 0; j < Z::EA; ++j) p.ea[j] = a[Z::ES + j];
 #pragma unroll
-  for (int j = 1; j <= Q; ++j) p.os[j] = a[2 * Q + j];
+  for (int j = 0; j < Z::OS; ++j) p.os[j] = a[Z::ES + Z::EA + j];
 #pragma unroll
-  for (int j = 1; j < Q; ++j) p.oa[j] = a[3 * Q + j];
+  for (int j = 0; j < Z::OA; ++j) p.oa[j] = a[Z::ES + Z::EA + Z::OS + j];
 }
 
 // c = U^T a in the block-ordered eigenbasis of T (positions -> modes)

@@ -6,7 +6,7 @@
 namespace ufg {
 
 // y = W_d x (adjoint: W_d^T x) of the plan on a lattice with the block form of
-// U (dimension 3, nx in {8, 12, 16}); with `src`, x is formed as described at
+// U (dimension 3, nx = 6 to 16); with `src`, x is formed as described at
 // PcSource. Counts its M0^{-1} applications.
 template <typename R>
 int wce_modes_apply(Lattice& L, const PcPlan& pc, bool adjoint, const C2<R>* x, C2<R>* y,

@@ -1,5 +1,5 @@
 // Weak-coupling series W_d (paper, Sec. 3) on lattices with the block form of
-// the eigenbasis U of T (dimension 3, Nx in {8, 12, 16}).
+// the eigenbasis U of T (dimension 3, Nx = 6 to 16).
 //
 // M0^{-1} = U^3 (1 - lam Z)^{-1} U^3T: a basis change per time slice, the
 // antiperiodic recurrence u_t = v_t + lam u_{t-1}, u_{-1} = -u_{Ntau-1} per mode,
@@ -446,8 +446,11 @@ int launch_last(const Lattice& L, const WceArgs<R>& a, int nslab) {
 
 #define WCE_NX(CALL)                                                             \
   switch (L.nx) {                                                                \
+    case 6: return CALL(6);                                                      \
     case 8: return CALL(8);                                                      \
+    case 10: return CALL(10);                                                    \
     case 12: return CALL(12);                                                    \
+    case 14: return CALL(14);                                                    \
     case 16: return CALL(16);                                                    \
     default: set_error("weak-coupling kernels: unsupported nx"); return UFG_EINVAL; \
   }

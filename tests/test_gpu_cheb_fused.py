@@ -1,8 +1,9 @@
 """The one-launch M^T M of the Chebyshev factors against the oracle: time
 extents of 2 and 3 (every neighbour wraps), extents that leave a short last
 workgroup, an odd number of factors and an even one (the vectors alternate),
-and both sides of the rules that choose the slices per workgroup (Nx = 8: 2048
-slices in all, Nx = 12: 512).
+and both sides of the rules that choose the slices per workgroup (Nx = 6, 8:
+2048 slices in all, Nx = 10, 12: 512, complex64 Nx = 14: 1024) or two launches
+(complex128 Nx = 14 above 512).
 
 Tolerances as for every Chebyshev application: complex128 1e-12, complex64 2e-4.
 """
@@ -22,7 +23,8 @@ TOL = {torch.complex128: 1e-12, torch.complex64: 2e-4}
 @pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
 @pytest.mark.parametrize("nx,ntau,nrhs", [
     (8, 2, 1), (8, 3, 2), (8, 10, 3), (8, 2049, 1), (12, 2, 1), (12, 7, 3), (12, 514, 1),
-    (16, 2, 2), (16, 5, 1),
+    (16, 2, 2), (16, 5, 1), (6, 2, 1), (6, 9, 2), (6, 2050, 1), (10, 4, 2), (10, 514, 1),
+    (14, 3, 2), (14, 513, 1), (14, 1026, 1),
 ])
 def test_chebyshev_fused(nx, ntau, nrhs, dtype):
     require_gpu()

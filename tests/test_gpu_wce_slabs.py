@@ -22,6 +22,7 @@ TOL = {torch.complex128: 1e-12, torch.complex64: 2e-5}
 @pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
 @pytest.mark.parametrize("nx,ntau,nrhs,slabs", [
     (8, 7, 3, (1, 2, 3, 7)), (12, 6, 1, (1, 4, 6)), (16, 9, 2, (1, 2, 4, 8, 9)), (8, 2, 1, (1, 2)),
+    (6, 7, 2, (1, 2, 3, 7)), (10, 5, 3, (1, 2, 5)), (14, 5, 1, (1, 3)),
     (16, 150, 2, (1,)),   # 64-column scan, more than 8 x 16 slabs
     (8, 600, 1, (1,)),    # 16-column scan, more than 32 x 16 slabs
 ])

@@ -37,7 +37,7 @@ void DevBuf::release() {
 int FlagMirror::ensure(int n) {
   if (host && n <= cap) return UFG_OK;
   release();
-  if (hipHostMalloc(reinterpret_cast<void**>(&host), 2 * sizeof(int) * n,
+  if (hipHostMalloc(reinterpret_cast<void**>(&host), 3 * sizeof(int) * n,
                     hipHostMallocDefault) != hipSuccess) {
     host = nullptr;
     (void)hipGetLastError();

@@ -358,7 +358,8 @@ __global__ void __launch_bounds__(256) finalize_kernel(int op, const double* par
                                                        int stride, const double* part2,
                                                        int nblk2, RhsState* st, int* active,
                                                        int* update, int* restart,
-                                                       const int* gate, KrylovParams prm) {
+                                                       const int* gate, KrylovParams prm,
+                                                       int* mirror) {
   const int k = blockIdx.x;
   if (gate && !gate[k]) return;
   // the state is fetched while the partials are summed
@@ -409,6 +410,7 @@ __global__ void __launch_bounds__(256) finalize_kernel(int op, const double* par
   apply_fin(op, s, q, act, upd, rst, prm);
   st[k] = q;
   active[k] = act;
+  if (mirror) mirror[k] = act;
   update[k] = upd;
   restart[k] = rst;
 }
@@ -612,10 +614,12 @@ int k_finalize(const Lattice& L, int op, int nblk, const int* gate, const Krylov
   }
   if (stride == 8 || nblk2 > 0)
     hipLaunchKernelGGL(finalize_kernel<8>, dim3(K.nrhs), dim3(256), 0, L.stream, op, K.part, nblk,
-                       stride, K.part2, nblk2, K.st, K.active, K.update, K.restart, gate, K.prm);
+                       stride, K.part2, nblk2, K.st, K.active, K.update, K.restart, gate, K.prm,
+                       K.mirror);
   else
     hipLaunchKernelGGL(finalize_kernel<4>, dim3(K.nrhs), dim3(256), 0, L.stream, op, K.part, nblk,
-                       stride, K.part2, nblk2, K.st, K.active, K.update, K.restart, gate, K.prm);
+                       stride, K.part2, nblk2, K.st, K.active, K.update, K.restart, gate, K.prm,
+                       K.mirror);
   UFG_HIP(hipGetLastError());
   return UFG_OK;
 }

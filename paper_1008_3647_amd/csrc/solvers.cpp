@@ -26,11 +26,11 @@ namespace ufg {
 
 namespace {
 
-// One check interval of a solver's iterations, captured once on a private
+// A check interval of a solver's iterations, or a piece of one, captured once on a private
 // stream and replayed on the lattice's stream. Small lattices run hundreds of
 // short launches per interval; a replay submits them at once. The body must
-// hold kernel launches only (no allocation, memset or copy): it runs after the
-// first interval has been launched eagerly, so every workspace and function
+// hold kernel launches only (no allocation, memset or copy): it is captured after the
+// same launches have been issued eagerly, so every workspace and function
 // attribute exists already. Counters advanced by the host code of the body are
 // counted per replay.
 struct IntervalGraph {
@@ -182,6 +182,8 @@ int bicgstab_step(Lattice& L, const PcPlan& pc, int op, const C2<RO>* b, C2<RO>*
   // spectra; the Q-type preconditioners composed with M^T or M make the
   // preconditioned operator Hermitian-like, where the limit only slows it.
   K.prm.limit_omega = (pc.kind == UFG_PC_NONE || pc.kind == UFG_PC_WCE) ? 1 : 0;
+  UFG_TRY(L.flags.ensure(3 * nrhs));
+  K.mirror = L.flags.poll();
   const int nvb = vec_blocks(L, nrhs);
   const int nhb = hop_blocks_per_rhs(L);
   const double2 one{1.0, 0.0}, zero{0.0, 0.0};
@@ -314,24 +316,72 @@ int bicgstab_step(Lattice& L, const PcPlan& pc, int op, const C2<RO>* b, C2<RO>*
   // Check points do not wait for the device. The reliable update and the
   // restart are issued at every check point as launches gated per rhs by
   // their device flags; the flags are then copied behind them to pinned host
-  // memory, which the host reads at the next check point, when that copy has
-  // long completed. The loop so ends one check interval late, on launches that
-  // do nothing (every rhs is inactive by then).
-  UFG_TRY(L.flags.ensure(3 * nrhs));
+  // memory. The fused form reads them at the next check point, when that copy
+  // has long completed, and so ends one check interval late, on launches that do
+  // nothing (every rhs is inactive by then). The unfused form issues its
+  // intervals in pieces of a few iterations and has one piece queued whenever
+  // it waits: it reads a check point's flags behind the first piece of the next
+  // interval, and the active flags, which the finalize kernels keep in pinned
+  // memory, behind every other one, and leaves out the rest of an interval
+  // once every rhs has stopped (a launch that does nothing still takes 2.5 us: a
+  // weak-coupling solve of 22 iterations at 12^3 x 200 issued 39).
   int posted = 0;
   Counters at_prev_post;  // the counters when the previous flags were posted
+  auto all_idle = [&](const volatile int* f) {
+    for (int i = 0; i < nrhs; ++i)
+      if (f[i]) return false;
+    return true;
+  };
   IntervalGraph G;
+  const int piece = std::min(check, need_pc ? 2 : 5);
+  Counters per_it;  // what one iteration adds to the counters
+  int pieces = 0;
+  auto classic_interval = [&](int len) -> int {
+    for (int k = 0; k < len; k += piece) {
+      const int n = std::min(piece, len - k);
+      // whole pieces after the first one replay a captured graph
+      if (!o.eager && n == piece && pieces > 0) {
+        if (!G.e) {
+          UFG_TRY(G.capture(L, cnt, [&]() -> int {
+            for (int q = 0; q < piece; ++q) UFG_TRY(classic_iteration());
+            return UFG_OK;
+          }));
+        }
+        UFG_TRY(G.replay(L, cnt));
+      } else {
+        for (int q = 0; q < n; ++q) {
+          const Counters c0 = *cnt;
+          UFG_TRY(classic_iteration());
+          per_it = Counters{cnt->mv - c0.mv, cnt->m0inv - c0.m0inv, cnt->sca - c0.sca};
+        }
+      }
+      UFG_HIP(hipEventRecord(L.flags.ev[2 + (pieces & 1)], L.stream));
+      ++pieces;
+      if (k == 0) {
+        if (posted > 0) {  // the check point this interval follows
+          const int prev = (posted - 1) & 1;
+          UFG_HIP(hipEventSynchronize(L.flags.ev[prev]));
+          if (all_idle(L.flags.host + prev * L.flags.cap)) {
+            done = true;
+            *cnt = at_prev_post;  // what was issued since then did no work
+            return UFG_OK;
+          }
+        }
+        continue;
+      }
+      UFG_HIP(hipEventSynchronize(L.flags.ev[2 + (pieces & 1)]));  // the piece before
+      if (all_idle(L.flags.poll())) {
+        const long long left = len - k - n;  // counted as issued
+        cnt->mv += left * per_it.mv;
+        cnt->m0inv += left * per_it.m0inv;
+        cnt->sca += left * per_it.sca;
+        return UFG_OK;
+      }
+    }
+    return UFG_OK;
+  };
   for (it = 0; it < o.maxit && !done; ++it) {
     const bool check_it = (it + 1) % check == 0 || it + 1 == o.maxit;
-    // a whole check interval after the first one: replay the captured interval
-    const bool replay = !fused && !o.eager && it >= check && it % check == 0 &&
-                        it + check <= o.maxit;
-    if (replay && !G.e) {
-      UFG_TRY(G.capture(L, cnt, [&]() -> int {
-        for (int k = 0; k < check; ++k) UFG_TRY(classic_iteration());
-        return UFG_OK;
-      }));
-    }
     if (fused) {
       HopArgs<RI> a1;  // v = A p; <rhat, v>
       a1.mat = F.T;
@@ -407,11 +457,11 @@ int bicgstab_step(Lattice& L, const PcPlan& pc, int op, const C2<RO>* b, C2<RO>*
         merged = true;
       }
       cnt->mv += 2;
-    } else if (replay) {
-      UFG_TRY(G.replay(L, cnt));
-      it += check - 1;  // the interval ends at the check point below
     } else {
-      UFG_TRY(classic_iteration());
+      const int len = std::min(check, o.maxit - it);
+      UFG_TRY(classic_interval(len));
+      if (done) break;
+      it += len - 1;  // the interval ends at the check point below
     }
     if ((it + 1) % check == 0 || it + 1 == o.maxit) {
       UFG_TRY(reliable_update());
@@ -423,13 +473,10 @@ int bicgstab_step(Lattice& L, const PcPlan& pc, int op, const C2<RO>* b, C2<RO>*
       UFG_HIP(hipEventRecord(L.flags.ev[slot], L.stream));
       ++posted;
       const Counters at_post = *cnt;
-      if (posted >= 2) {  // the previous check point's flags
+      if (fused && posted >= 2) {  // the previous check point's flags
         const int prev = slot ^ 1;
         UFG_HIP(hipEventSynchronize(L.flags.ev[prev]));
-        const int* f = L.flags.host + prev * L.flags.cap;
-        done = true;
-        for (int i = 0; i < nrhs; ++i)
-          if (f[i]) done = false;
+        done = all_idle(L.flags.host + prev * L.flags.cap);
         // every rhs was inactive when those flags were taken: what was issued
         // since then did no work and is not counted
         if (done) *cnt = at_prev_post;

@@ -74,11 +74,13 @@ struct DevBuf {
 };
 
 // Pinned host mirror of solver flags: two slots of `cap` ints, each with an
-// event recorded behind the copy into it.
+// event recorded behind the copy into it, and a third area of `cap` ints that
+// the finalize kernels write themselves (poll()), with two events for its use.
 struct FlagMirror {
   int* host = nullptr;
   int cap = 0;
-  hipEvent_t ev[2] = {nullptr, nullptr};
+  hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
+  int* poll() const { return host + 2 * cap; }
   int ensure(int n);
   void release();
   ~FlagMirror() { release(); }

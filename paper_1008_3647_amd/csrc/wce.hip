@@ -303,57 +303,58 @@ __device__ __forceinline__ double ipow(double x, int n) {
 // lam^len_j U_{j-1}, U_{-1} = -U_last. MODES columns along the lanes x CHUNKS
 // chunks of slabs per workgroup; a chunk of up to KEEP slabs stays in registers
 // between the two sweeps. Every thread walks all chunk sums by itself (one
-// barrier, no serial section of one chunk's threads). FP64 whatever the vector
-// type.
-template <typename R, int MODES, int CHUNKS>
+// barrier, no serial section of one chunk's threads), from sums that are all
+// read at once. FP64 whatever the vector type. Small and bound by its latency:
+// a column per (grid.y, lane), no division, buffer loads whose range check does
+// for the ends of a chunk (a launch at 12^3 x 200: 6.5 us with 64-bit column
+// numbers and addresses, 32 chunks and a loop over their sums; 4.0 us so).
+template <typename R, int MODES, int CHUNKS, int KEEP>
 __global__ void __launch_bounds__(MODES* CHUNKS)
     wce_scan_kernel(R* carry, const double* __restrict__ lam_mode, int V, int ntau, int slab,
-                    int nslab, int nrhs, int adjoint, const int* gate) {
-  constexpr int KEEP = sizeof(R) == 4 ? 16 : 8;
+                    int nslab, int adjoint, const int* gate) {
   __shared__ double cend[CHUNKS][MODES];
   __shared__ double cpow[CHUNKS][MODES];
+  constexpr int RS = sizeof(R);
+  const int r = blockIdx.y >> 1, comp = blockIdx.y & 1;
+  if (gate && gate[r] == 0) return;
   const int ml = threadIdx.x % MODES, c = threadIdx.x / MODES;
-  const long long gid = (long long)blockIdx.x * MODES + ml;
-  const bool inb = gid < 2ll * V * nrhs;
-  const int rc = inb ? int(gid / V) : 0;
-  const int n = inb ? int(gid - (long long)rc * V) : 0;
-  const bool act = inb && !(gate && gate[rc >> 1] == 0);
+  const int n = blockIdx.x * MODES + ml;
+  const bool inb = n < V;
   const int Lc = (nslab + CHUNKS - 1) / CHUNKS;
-  const int k0 = min(c * Lc, nslab), k1 = min(k0 + Lc, nslab);
+  const int k0 = c * Lc, k1 = min(k0 + Lc, nslab);
   const int short_k = adjoint ? 0 : nslab - 1;  // sweep position of the slab that may be short
-  R* col = carry + (((long long)(rc >> 1) * nslab) * 2 + (rc & 1)) * V + n;
-  auto at = [&](int k) -> long long { return (long long)(adjoint ? nslab - 1 - k : k) * 2 * V; };
-  double lamS = 0.0, lamL = 0.0, pw = 1.0, w = 0.0;
+  // out of range (k >= k1, n >= V) is past the end of the buffer: reads zero, stores nothing
+  const auto rc = make_rsrc(carry + (long long)r * nslab * 2 * V, nslab * 2 * V * RS);
+  const int step = (adjoint ? -2 : 2) * V * RS;
+  const int o0 = (((adjoint ? nslab - 1 - k0 : k0) * 2 + comp) * V + n) * RS;
+  const int none = nslab * 2 * V * RS;
+  auto at = [&](int k) { return inb && k < k1 ? o0 + (k - k0) * step : none; };
   R G[KEEP];
-  if (act) {
 #pragma unroll
-    for (int i = 0; i < KEEP; ++i)
-      if (k0 + i < k1) G[i] = col[at(k0 + i)];
-    const double lam = lam_mode[n];
-    lamS = ipow(lam, slab);
-    lamL = ipow(lam, ntau - (nslab - 1) * slab);
+  for (int i = 0; i < KEEP; ++i) G[i] = bload_real<R>(rc, at(k0 + i), 0);
+  const double lam = inb ? lam_mode[n] : 0.0;
+  const double lamS = ipow(lam, slab), lamL = ipow(lam, ntau - (nslab - 1) * slab);
+  double pw = 1.0, w = 0.0;
 #pragma unroll
-    for (int i = 0; i < KEEP; ++i) {
-      if (k0 + i < k1) {
-        const double p = k0 + i == short_k ? lamL : lamS;
-        w = double(G[i]) + p * w;
-        pw *= p;
-      }
-    }
-#pragma unroll 4
-    for (int k = k0 + KEEP; k < k1; ++k) {
-      const double p = k == short_k ? lamL : lamS;
-      w = double(col[at(k)]) + p * w;
+  for (int i = 0; i < KEEP; ++i) {
+    if (k0 + i < k1) {
+      const double p = k0 + i == short_k ? lamL : lamS;
+      w = double(G[i]) + p * w;
       pw *= p;
     }
+  }
+#pragma unroll 4
+  for (int k = k0 + KEEP; k < k1; ++k) {
+    const double p = k == short_k ? lamL : lamS;
+    w = double(bload_real<R>(rc, at(k), 0)) + p * w;
+    pw *= p;
   }
   cend[c][ml] = w;
   cpow[c][ml] = pw;
   __syncthreads();
-  if (!act) return;
   // U: the scan over all chunks from zero; v, pv: its value and power before chunk c
   double U = 0.0, v = 0.0, lamN = 1.0, pv = 1.0;
-#pragma unroll 8
+#pragma unroll
   for (int j = 0; j < CHUNKS; ++j) {
     if (j == c) {
       v = U;
@@ -366,29 +367,26 @@ __global__ void __launch_bounds__(MODES* CHUNKS)
   v -= pv * U / (1.0 + lamN);  // U_{-1} = -U / (1 + lam^Ntau), carried to chunk c
 #pragma unroll
   for (int i = 0; i < KEEP; ++i) {
-    if (k0 + i < k1) {
-      const double p = k0 + i == short_k ? lamL : lamS;
-      col[at(k0 + i)] = R(v);
-      v = double(G[i]) + p * v;
-    }
+    bstore_real<R>(R(v), rc, at(k0 + i), 0);
+    const double p = k0 + i == short_k ? lamL : lamS;
+    v = double(G[i]) + p * v;
   }
 #pragma unroll 4
   for (int k = k0 + KEEP; k < k1; ++k) {
-    const long long i = at(k);
-    const R g = col[i];
+    const R g = bload_real<R>(rc, at(k), 0);
     const double p = k == short_k ? lamL : lamS;
-    col[i] = R(v);
+    bstore_real<R>(R(v), rc, at(k), 0);
     v = double(g) + p * v;
   }
 }
 
-template <typename R, int MODES, int CHUNKS>
+template <typename R, int MODES, int CHUNKS, int KEEP>
 int launch_scan_shape(const Lattice& L, R* carry, int slab, int nslab, int nrhs, bool adjoint,
                       const int* gate) {
-  const long long n = 2ll * L.V * nrhs;
-  hipLaunchKernelGGL((wce_scan_kernel<R, MODES, CHUNKS>), dim3((unsigned)((n + MODES - 1) / MODES)),
+  hipLaunchKernelGGL((wce_scan_kernel<R, MODES, CHUNKS, KEEP>),
+                     dim3((unsigned)((L.V + MODES - 1) / MODES), (unsigned)(2 * nrhs)),
                      dim3(MODES * CHUNKS), 0, L.stream, carry, L.f64.lam, L.V, L.ntau, slab, nslab,
-                     nrhs, adjoint ? 1 : 0, gate);
+                     adjoint ? 1 : 0, gate);
   UFG_HIP(hipGetLastError());
   return UFG_OK;
 }
@@ -396,9 +394,16 @@ int launch_scan_shape(const Lattice& L, R* carry, int slab, int nslab, int nrhs,
 template <typename R>
 int launch_scan(const Lattice& L, R* carry, int slab, int nslab, int nrhs, bool adjoint,
                 const int* gate) {
+  // Many columns: wide rows, short chunks. Few: 16 modes a row to have more
+  // workgroups, and chunks that fit the registers. Order-2 application, us, with
+  // 32 x 8 keeping 8 / 16 x 8 keeping 16 / 16 x 16 keeping 16: 16^3 x 400, 8 rhs (80
+  // slabs) complex64 274 / 293 / 285 (32 x 16); 8^3 x 160, 4 rhs (80 slabs) 42.0 / 39.8 /
+  // 41.3; 6^3 x 50 (50) 20.9 / 21.1 / 23.4; 12^3 x 200 (200) 65.5 / 58.6 / 53.0.
   if (2ll * L.V * nrhs >= 64 * 256)
-    return launch_scan_shape<R, 64, 8>(L, carry, slab, nslab, nrhs, adjoint, gate);
-  return launch_scan_shape<R, 16, 32>(L, carry, slab, nslab, nrhs, adjoint, gate);
+    return launch_scan_shape<R, 32, 8, 8>(L, carry, slab, nslab, nrhs, adjoint, gate);
+  if (nslab <= 128)
+    return launch_scan_shape<R, 16, 8, 16>(L, carry, slab, nslab, nrhs, adjoint, gate);
+  return launch_scan_shape<R, 16, 16, 16>(L, carry, slab, nslab, nrhs, adjoint, gate);
 }
 
 // The blocks of U^T and U, adjacent on the device.
@@ -483,18 +488,20 @@ int last_change(const Lattice& L, const WceArgs<R>& a, int nslab) {
 }  // namespace
 
 int wce_slab(const Lattice& L, int nrhs) {
-  if (L.nslab > 0) return (L.ntau + L.nslab - 1) / L.nslab;  // nslab <= ntau
-  if (L.slab > 0) return std::min(L.slab, L.ntau);
+  // the scan addresses one rhs's slab ends by 32-bit byte offsets: keep them below 2 GiB
+  const int least = 1 + (int)(((long long)L.ntau * 2 * L.V * 8) >> 30);
+  if (L.nslab > 0) return std::max(least, (L.ntau + L.nslab - 1) / L.nslab);  // nslab <= ntau
+  if (L.slab > 0) return std::max(least, std::min(L.slab, L.ntau));
   // Longer slabs make the scan cheaper (its traffic is 1 / slab of a pass) and
   // each launch longer (a slab's slices run one after the other); with n slices
   // in all the balance lies near sqrt(n / 128). Order-2 application, us at slab
-  // 1 / 2 / 4 / 5 / 8: 16^3 x 400, 8 rhs (n = 3200) complex64 456 / 347 / 299 /
-  // 282 / 301, complex128 969 / 707 / 638 / 596 / 625; 12^3 x 200, 8 rhs (1600)
-  // complex128 184 / 155 / 146 / 154 / 181; 8^3 x 160, 4 rhs (640) 50 / 47 / 53 /
-  // 56 / 71; 16^3 x 400, 1 rhs (400) complex64 96 / 89 / 105 / 117 / 161; 12^3 x
-  // 200, 1 rhs (200) complex128 62 / 66 / 92 / 104 / 152.
+  // 1 / 2 / 4 / 5 / 8: 16^3 x 400, 8 rhs (n = 3200) complex64 453 / 345 / 293 /
+  // 275 / 287, complex128 985 / 726 / 652 / 610 / 636; 12^3 x 200, 8 rhs (1600)
+  // complex128 180 / 148 / 144 / 153 / 180; 8^3 x 160, 4 rhs (640) 44 / 40 / 46 /
+  // 48 / 64; 16^3 x 400, 1 rhs (400) complex64 89 / 81 / 96 / 108 / 150; 12^3 x
+  // 200, 1 rhs (200) complex128 55 / 57 / 83 / 93 / 139.
   const double n = (double)L.ntau * nrhs;
-  return std::min(8, std::max(1, (int)std::lround(std::sqrt(n / 128.0))));
+  return std::max(least, std::min(8, (int)std::lround(std::sqrt(n / 128.0))));
 }
 
 template <typename R>

@@ -1,7 +1,7 @@
 """The fused weak-coupling launches at every shape of their slab split against
 the oracle: slabs of 1, of lengths that leave a short last slab, of the whole
 time extent, and scans whose chunks of slabs exceed what a thread keeps in
-registers (8 slabs in FP64, 16 in FP32, times 8 or 32 chunks).
+registers (8 slabs times 8 chunks, or 16 times 16).
 
 Tolerances as for every weak-coupling application (element-wise, relative to
 the largest output): complex128 1e-12, complex64 2e-5.
@@ -23,8 +23,8 @@ TOL = {torch.complex128: 1e-12, torch.complex64: 2e-5}
 @pytest.mark.parametrize("nx,ntau,nrhs,slabs", [
     (8, 7, 3, (1, 2, 3, 7)), (12, 6, 1, (1, 4, 6)), (16, 9, 2, (1, 2, 4, 8, 9)), (8, 2, 1, (1, 2)),
     (6, 7, 2, (1, 2, 3, 7)), (10, 5, 3, (1, 2, 5)), (14, 5, 1, (1, 3)),
-    (16, 150, 2, (1,)),   # 64-column scan, more than 8 x 16 slabs
-    (8, 600, 1, (1,)),    # 16-column scan, more than 32 x 16 slabs
+    (16, 150, 2, (1,)),   # 32-column scan, more than 8 x 8 slabs
+    (8, 600, 1, (1,)),    # 16-column scan, more than 16 x 16 slabs
 ])
 def test_wce_slabs(nx, ntau, nrhs, slabs, dtype):
     require_gpu()

@@ -18,7 +18,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libufg.so")
 EXAMPLES = os.path.join(HERE, "examples")
 SOURCES = ["api.cpp", "ops.cpp", "solvers.cpp", "split.cpp", "batched.hip", "hop.hip",
-           "hop_stream.hip", "hop_q.hip", "wce.hip", "temporal.hip", "krylov.hip", "noalloc.hip",
+           "hop_stream.hip", "hop_q.hip", "force.hip", "wce.hip", "temporal.hip", "krylov.hip", "noalloc.hip",
            "hmc.hip", "lowd.hip"]
 ARCH = "gfx950"
 

@@ -125,7 +125,7 @@ static void transfer_eigenbasis(int nx, double tau, int dispersion, double* U, d
 static int alloc_fields(Lattice& L) {
   const size_t N = (size_t)L.N;
   double** d[] = {&L.f64.b, &L.f64.sn, &L.f64.cs, &L.f64.scaD, &L.f64.scaL};
-  float** f[] = {&L.f32.b, &L.f32.sn, &L.f32.cs, &L.f32.scaD, &L.f32.scaL};
+  float** f[] = {&L.f32.b, &L.f32.sn, &L.f32.scaD, &L.f32.scaL};
   for (auto pp : d)
     if (hipMalloc(pp, N * sizeof(double)) != hipSuccess) return UFG_ENOMEM;
   for (auto pp : f)
@@ -139,7 +139,7 @@ static int alloc_fields(Lattice& L) {
 
 static void free_fields(Lattice& L) {
   void* ptrs[] = {L.f64.b, L.f64.sn, L.f64.cs, L.f64.scaD, L.f64.scaL, L.f32.b, L.f32.sn,
-                  L.f32.cs, L.f32.scaD, L.f32.scaL, L.sigma, L.f64.T, L.f32.T};
+                  L.f32.scaD, L.f32.scaL, L.sigma, L.f64.T, L.f32.T};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (L.bmax_host) (void)hipHostFree(L.bmax_host);

@@ -124,7 +124,7 @@ __global__ void __launch_bounds__(HopShape<NX>::THREADS)
 template <typename R, int NX>
 __global__ void __launch_bounds__(HopShape<NX>::THREADS)
     force_kernel(const C2<R>* __restrict__ X, const C2<R>* __restrict__ y, const R* __restrict__ mat,
-                 const double* __restrict__ sigma, double A, int ntau, int nrhs, double* grad) {
+                 const double* __restrict__ cs, double A, int ntau, int nrhs, double* grad) {
   using S = HopShape<NX>;
   constexpr int P = S::P, V = S::V, SPW = S::SPW;
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(HopShape<NX>::THREADS)
 #pragma unroll
     for (int z = 0; z < NX; ++z) {
       const long long i = (long long)t * V + z * P + l;
-      grad[i] = -2.0 * A * cos(sigma[i]) * sgn * acc[z];
+      grad[i] = -2.0 * A * cs[i] * sgn * acc[z];
     }
   }
 }
@@ -212,7 +212,7 @@ int launch_force_nx(const Lattice& L, const C2<R>* X, const C2<R>* y, int nrhs, 
   }
   const Fields<R>& F = fields<R>(L);
   hipLaunchKernelGGL((force_kernel<R, NX>), dim3(tgroups), dim3(S::THREADS), lds, L.stream, X, y,
-                     F.T, L.sigma, L.A, L.ntau, nrhs, grad);
+                     F.T, L.f64.cs, L.A, L.ntau, nrhs, grad);
   UFG_HIP(hipGetLastError());
   return UFG_OK;
 }
@@ -255,9 +255,12 @@ int hop_blocks_per_rhs(const Lattice& L) {
 template <typename R>
 int launch_force(const Lattice& L, const C2<R>* X, const C2<R>* y, int nrhs, double* grad) {
   if (L.dim < 3) return launch_force_lowd<R>(L, X, y, nrhs, grad);
-#define CALL_F(NX) launch_force_nx<R, NX>(L, X, y, nrhs, grad)
-  UFG_NX_SWITCH(L.nx, CALL_F)
-#undef CALL_F
+  // Nx = 2 and 4 have no block form and put several slices in a workgroup
+  if (!L.split_host.empty()) return launch_force_block<R>(L, X, y, nrhs, grad);
+  if (L.nx == 2) return launch_force_nx<R, 2>(L, X, y, nrhs, grad);
+  if (L.nx == 4) return launch_force_nx<R, 4>(L, X, y, nrhs, grad);
+  set_error("unsupported nx");
+  return UFG_EINVAL;
 }
 
 template int launch_hop<float>(const Lattice&, const HopArgs<float>&);

@@ -235,7 +235,7 @@ __global__ void __launch_bounds__(kLowdThreads) hop_lowd_kernel(HopArgs<R> a, in
 template <typename R, int NX, int D>
 __global__ void __launch_bounds__(kLowdThreads)
     force_lowd_kernel(const C2<R>* __restrict__ X, const C2<R>* __restrict__ y,
-                      const R* __restrict__ mat, const double* __restrict__ sigma, double A,
+                      const R* __restrict__ mat, const double* __restrict__ cs, double A,
                       int ntau, int nrhs, double* grad) {
   using S = LowdShape<NX, D>;
   constexpr int V = S::V, SPW = S::SPW;
@@ -264,7 +264,7 @@ __global__ void __launch_bounds__(kLowdThreads)
   if (valid) {
     const double sgn = (t == ntau - 1) ? 1.0 : -1.0;
     const long long i = (long long)t * V + l;
-    grad[i] = -2.0 * A * cos(sigma[i]) * sgn * acc;
+    grad[i] = -2.0 * A * cs[i] * sgn * acc;
   }
 }
 
@@ -292,7 +292,7 @@ int launch_force_lowd_nx(const Lattice& L, const C2<R>* X, const C2<R>* y, int n
   const int tgroups = (L.ntau + S::SPW - 1) / S::SPW;
   const Fields<R>& F = fields<R>(L);
   hipLaunchKernelGGL((force_lowd_kernel<R, NX, D>), dim3(tgroups), dim3(kLowdThreads), 0,
-                     L.stream, X, y, F.T, L.sigma, L.A, L.ntau, nrhs, grad);
+                     L.stream, X, y, F.T, L.f64.cs, L.A, L.ntau, nrhs, grad);
   UFG_HIP(hipGetLastError());
   return UFG_OK;
 }

@@ -16,20 +16,19 @@ namespace {
 // `sigma` is copied to `own` on the way (null: it is the library's copy already).
 __global__ void field_setup_kernel(const double* __restrict__ sigma, double* own, double A,
                                    long long n, double* b64, double* s64, double* c64, float* b32, float* s32,
-                                   float* c32, double* bmax_part) {
+                                   double* bmax_part) {
   double m = 0.0;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
        i += (long long)gridDim.x * blockDim.x) {
     const double sg = sigma[i];
     if (own) own[i] = sg;
-    const double s = sin(sg), c = cos(sg);
+    double s, c; sincos(sg, &s, &c);
     const double b = 1.0 + A * s;
     b64[i] = b;
     s64[i] = s;
     c64[i] = c;
     b32[i] = float(b);
     s32[i] = float(s);
-    c32[i] = float(c);
     m = fmax(m, fabs(b));
   }
   for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
@@ -402,7 +401,7 @@ __global__ void __launch_bounds__(kModes* kChunks)
 int launch_field_setup(Lattice& L, const double* sigma, double* bmax_part, int nblk) {
   hipLaunchKernelGGL(field_setup_kernel, dim3(nblk), dim3(256), 0, L.stream, sigma,
                      sigma == L.sigma ? nullptr : L.sigma, L.A, L.N, L.f64.b, L.f64.sn, L.f64.cs,
-                     L.f32.b, L.f32.sn, L.f32.cs, bmax_part);
+                     L.f32.b, L.f32.sn, bmax_part);
   UFG_HIP(hipGetLastError());
   return UFG_OK;
 }

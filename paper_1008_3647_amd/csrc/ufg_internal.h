@@ -53,7 +53,7 @@ template <typename R>
 struct Fields {
   R* b = nullptr;       // 1 + A sin sigma                 [N]
   R* sn = nullptr;      // sin sigma                       [N]
-  R* cs = nullptr;      // cos sigma                       [N]
+  R* cs = nullptr;      // cos sigma (FP64 only: the force)  [N]
   R* scaD = nullptr;    // strong coupling D_t             [N]
   R* scaL = nullptr;    // strong coupling L_t             [N]
   R* T = nullptr;       // 1D factor of exp(-tau K)        [nx*nx]
@@ -217,6 +217,10 @@ int launch_force_lowd(const Lattice& L, const C2<R>* X, const C2<R>* y, int nrhs
 // c = -2 A cos sigma.
 template <typename R>
 int launch_force(const Lattice& L, const C2<R>* X, const C2<R>* y, int nrhs, double* grad);
+
+// Its form for lattices with the block form of T (force.hip); launch_force routes there.
+template <typename R>
+int launch_force_block(const Lattice& L, const C2<R>* X, const C2<R>* y, int nrhs, double* grad);
 
 // Temporal kernels.
 template <typename R>

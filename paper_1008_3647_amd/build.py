@@ -19,7 +19,7 @@ LIB = os.path.join(HERE, "libufg.so")
 EXAMPLES = os.path.join(HERE, "examples")
 SOURCES = ["api.cpp", "ops.cpp", "solvers.cpp", "split.cpp", "batched.hip", "hop.hip",
            "hop_stream.hip", "hop_q.hip", "force.hip", "wce.hip", "temporal.hip", "krylov.hip", "noalloc.hip",
-           "hmc.hip", "lowd.hip"]
+           "hmc.hip", "lowd.hip", "lowd_line.hip"]
 ARCH = "gfx950"
 
 

@@ -284,9 +284,9 @@ int create_lattice_dim(int nx, int ntau, int dim, double tau, double g, int dtyp
     set_error("create_lattice: eigenbasis check failed");
     return UFG_EHIP;
   }
-  // block forms of T and U serve the streaming kernels (three-dimensional
-  // slices); lower dimensions use the general slice kernels with T and U
-  if (dim == 3 && split_coefficients(nx, L->T_host, &L->split_host) > 1e-13) {
+  // block form of T: the operators of every dimension and the force; block form of U:
+  // the weak-coupling launches (three-dimensional slices)
+  if (split_coefficients(nx, L->T_host, &L->split_host) > 1e-13) {
     free_fields(*L);
     delete L;
     set_error("create_lattice: block form of T failed its check");

@@ -775,7 +775,7 @@ bool stream_supported(const Lattice& L) {
   // 11.1, 14^3 x 400, 8 rhs complex128 100 / 108 -> 64 / 64, 6^3 x 800, 64 rhs complex64
   // 46.6 / 50.8 -> 42.9 / 43.1 (36 of a wave's 64 lanes hold a line there), 6^3 x 50
   // complex128 6.5 / 6.7 -> 6.2 / 6.3. Nx = 2 and 4 keep it: several slices to a wave.
-  return !L.split_host.empty() && block < (1ll << 31);
+  return L.dim == 3 && !L.split_host.empty() && block < (1ll << 31);
 }
 
 template <typename R>

@@ -318,12 +318,16 @@ int launch_hop_lowd(const Lattice& L, const HopArgs<R>& a) {
     set_error("slice kernel: lattice dimension must be 1 or 2 here");
     return UFG_EINVAL;
   }
+  // M and M^T with the kinetic factor T where it has a block form
+  if (a.shift != 0 && a.mat == fields<R>(L).T && lowd_line_supported(L))
+    return launch_hop_lowd_line<R>(L, a);
 #define CALL_LOWD(NX, D) launch_lowd<R, NX, D>(L, a)
   UFG_LOWD_SWITCH(CALL_LOWD)
 #undef CALL_LOWD
 }
 
 int lowd_blocks_per_rhs(const Lattice& L) {
+  if (lowd_line_supported(L)) return lowd_line_blocks(L);
   const int v = L.dim == 1 ? L.nx : L.nx * L.nx;
   const int per = (kLowdThreads / v) * lowd_slices(L.nx, L.dim);  // slices per workgroup
   return (L.ntau + per - 1) / per;

@@ -102,7 +102,7 @@ struct Lattice {
   Fields<double> f64;
   Fields<float> f32;
   std::vector<double> T_host, U_host, lam1_host;  // 1D factors (host)
-  std::vector<double> split_host;  // block-diagonal form of T (streaming kernel)
+  std::vector<double> split_host;  // block form of T (empty: Nx = 2, 4)
   std::vector<double> mode_fwd_host, mode_bwd_host;  // block form of U^T and U
   std::vector<int> mode_perm;       // block-ordered mode -> column of U
   int slab = 0;                    // time slices per workgroup of the streaming kernel (0: default)
@@ -210,6 +210,11 @@ int hop_blocks_per_rhs(const Lattice& L);
 template <typename R>
 int launch_hop_lowd(const Lattice& L, const HopArgs<R>& a);
 int lowd_blocks_per_rhs(const Lattice& L);
+// Its form for M and M^T where T has a block form (lowd_line.hip).
+bool lowd_line_supported(const Lattice& L);
+int lowd_line_blocks(const Lattice& L);  // reduction partials per rhs
+template <typename R>
+int launch_hop_lowd_line(const Lattice& L, const HopArgs<R>& a);
 template <typename R>
 int launch_force_lowd(const Lattice& L, const C2<R>* X, const C2<R>* y, int nrhs, double* grad);
 

@@ -406,26 +406,28 @@ int lattice_norm2_noalloc(ufg_lattice L, const void* x, int nrhs, double* out_de
 /*
  * lattice_tune -- launch parameters chosen by the autotuner (0 keeps the
  *   default): `slab` time slices per workgroup of the streaming M / M^T kernel
- *   (Nx = 6 to 16; 1..Ntau), `vec_blocks` workgroups per right-hand side of
- *   the Krylov vector kernels (1..4096). Results do not depend on them beyond
- *   floating-point summation order.
+ *   and of the weak-coupling launches (Nx = 6 to 16; 1..Ntau), `vec_blocks`
+ *   workgroups per right-hand side of the Krylov vector kernels (1..4096).
+ *   Results do not depend on them beyond floating-point summation order.
  */
 int lattice_tune(ufg_lattice L, int slab, int vec_blocks);
 
 /*
  * lattice_tune_slabs -- number of slabs per right-hand side of the streaming
- *   M / M^T kernel (1..Ntau; 0 derives it from lattice_tune's slab as
- *   ceil(Ntau / slab)). Slab s covers slices [s Ntau / n, (s + 1) Ntau / n), so
- *   the count need not divide Ntau; it sets the grid (n x nrhs workgroups) to fit
- *   the number of resident workgroups. Same result guarantee as lattice_tune.
+ *   M / M^T kernel and of the weak-coupling launches (1..Ntau; 0 derives it
+ *   from lattice_tune's slab as ceil(Ntau / slab)). Slab s covers slices
+ *   [s Ntau / n, (s + 1) Ntau / n), so the count need not divide Ntau; it sets
+ *   the grid (n x nrhs workgroups) to fit the number of resident workgroups
+ *   (the weak-coupling launches take slabs of ceil(Ntau / n) slices). Same
+ *   result guarantee as lattice_tune.
  */
 int lattice_tune_slabs(ufg_lattice L, int nslab);
 
 /*
- * lattice_tune_order -- workgroup numbering of the streaming M / M^T and
- *   basis-change kernels. group >= 1: groups of `group` consecutive slabs go
- *   round-robin to the eight XCDs, so a slab's halo slice and its field slab
- *   are read through one XCD's L2; each XCD takes its groups right-hand side
+ * lattice_tune_order -- workgroup numbering of the streaming M / M^T kernel.
+ *   group >= 1: groups of `group` consecutive slabs go round-robin to the
+ *   eight XCDs, so a slab's halo slice and its field slab are read through one
+ *   XCD's L2; each XCD takes its groups right-hand side
  *   by right-hand side (rhs_inner = 0) or, group by group, every right-hand
  *   side of a group in turn (rhs_inner = 1). group = 0: contiguous runs of
  *   (slab, rhs) pairs per XCD, rhs fastest (rhs_inner ignored); group = -1:

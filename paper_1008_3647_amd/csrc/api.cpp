@@ -286,7 +286,9 @@ int create_lattice_dim(int nx, int ntau, int dim, double tau, double g, int dtyp
   }
   // block form of T: the operators of every dimension and the force; block form of U:
   // the weak-coupling launches (three-dimensional slices)
-  if (split_coefficients(nx, L->T_host, &L->split_host) > 1e-13) {
+  const bool split_bad = split_coefficients(nx, L->T_host, &L->split_host) > 1e-13;
+  if (split_bad && dim < 3) L->split_host.clear();  // the general slice kernels take it
+  if (split_bad && dim == 3) {
     free_fields(*L);
     delete L;
     set_error("create_lattice: block form of T failed its check");

@@ -1,6 +1,9 @@
 // Slice operator and force for lattices of spatial dimension 1 and 2 (the
 // lower dimensions the paper's concluding section names as an extension).
 //
+// M and M^T of lattices where T has a block form run in lowd_line.hip; here are
+// the others (Nx = 2, 4, 2D Nx = 6, 2 GiB and more per rhs) and the basis changes.
+//
 // A slice has Nx (dimension 1) or Nx^2 (dimension 2) sites and exp(-tau K)
 // is T or T (x) T with the same symmetric circulant T as in three dimensions.
 // One thread per site of SPW = 256 / Nx^d slices of one right-hand side, and

@@ -2,16 +2,17 @@
 //
 // Preconditioners (paper):
 //   Chebyshev (Sec. 2): P(Q^) v = prod_k c^{1/2n} (Q/lam_max - z_k) v, roots in
-//     bit-reversal order; each factor is an M then an M^T launch whose epilogue
-//     does the complex axpby.
+//     bit-reversal order; a factor is one launch where hop_q.hip takes the lattice,
+//     else an M then an M^T launch whose epilogue does the complex axpby.
 //   Strong coupling (Sec. 4): (L^dagger D L)^{-1} by one per-site kernel.
 //   Weak coupling (Sec. 3): with T^3 = U^3 diag(lam) U^3T and M0 = 1 - Z T^3,
 //     M1 = -Z T^3 S (S = diag sin sigma, Z the antiperiodic one-slice shift):
 //       M0^{-1}          = U^3 (1 - lam Z)^{-1} U^3T
 //       -A M0^{-1} M1 u  = A U^3 [(1 - lam Z)^{-1} - 1] U^3T S u
 //       -A M1^T M0^{-T}v = A S U^3 [(1 - lam Z^T)^{-1} - 1] U^3T v
-//     so every order of the expansion costs two spatial basis changes and one
-//     temporal sweep, with the M1 factor folded into them.
+//     so every order of the expansion costs two spatial basis changes with the
+//     temporal recurrence between them (inside them in wce.hip) and the M1 factor
+//     folded into them.
 #include "ops.h"
 #include "hop_stream.h"
 #include "wce.h"

@@ -1,12 +1,14 @@
 // Kernels that run along Euclidean time at fixed spatial site or mode:
 //   * field setup: 1 + A sin sigma, sin sigma, cos sigma (paper, Sec. 1)
-//   * strong-coupling factorisation and its two sweeps (paper, Sec. 4)
+//   * strong-coupling factorisation and its two sweeps (paper, Sec. 4), the time
+//     line split into chunks that threads hold in registers
 //   * the temporal part of M0^{-1} in the eigenbasis of exp(-tau K)
 //     (paper, Sec. 3: M0 is diagonal in frequency-momentum space; per spatial
 //     mode the antiperiodic time problem (1 - lam Z) u = v has the closed form
-//     u = (1 + lam^Ntau)^{-1} sum_m lam^m Z^m v, evaluated by two sweeps).
-// One thread owns one (rhs, site) column; consecutive threads take consecutive
-// sites so every access along t is a coalesced row.
+//     u = (1 + lam^Ntau)^{-1} sum_m lam^m Z^m v, evaluated by two sweeps), for the
+//     lattices without the block form of U (wce.hip has the others)
+// Consecutive threads take consecutive sites so every access along t is a
+// coalesced row.
 #include "slice_t3.h"
 #include "ufg_internal.h"
 
@@ -22,7 +24,8 @@ __global__ void field_setup_kernel(const double* __restrict__ sigma, double* own
        i += (long long)gridDim.x * blockDim.x) {
     const double sg = sigma[i];
     if (own) own[i] = sg;
-    double s, c; sincos(sg, &s, &c);
+    double s, c;
+    sincos(sg, &s, &c);
     const double b = 1.0 + A * s;
     b64[i] = b;
     s64[i] = s;

@@ -6,6 +6,33 @@
 namespace ufg {
 namespace {
 
+// A complex64 lattice has its force in double precision too, and the rounding of
+// its FP32 transform stays what the dense product gives: the same terms in the
+// same order, one component at a time (16^3 x 400, 8 rhs 94 -> 72 us; the block form
+// 55 us, but 1.6e-7 away from the dense product's rounding).
+template <typename R, int NX>
+struct DenseT {
+  const R* p;  // T, row by row
+};
+template <int MODE, typename R, int NX>
+__device__ __forceinline__ void line_op(const DenseT<R, NX>& c, R (&v)[NX]) {
+  using CC = const __attribute__((address_space(4))) R;
+  CC* m = (CC*)c.p;
+  asm volatile("" : "+s"(m));
+  R w[NX];
+#pragma unroll
+  for (int i = 0; i < NX; ++i) {
+    R acc = R(0);
+#pragma unroll
+    for (int j = 0; j < NX; ++j) acc = fma(m[i * NX + j], v[j], acc);
+    w[i] = acc;
+  }
+#pragma unroll
+  for (int i = 0; i < NX; ++i) v[i] = w[i];
+}
+template <typename R, int NX>
+using ForceT = std::conditional_t<sizeof(R) == 4, DenseT<R, NX>, CoefPtr<R, NX>>;
+
 // A workgroup takes one slice t and all right-hand sides, one real component of
 // y and X per Nx^2 threads (T is real, and the real part of the product is the
 // sum over components), the two sums added through LDS at the end. One or a few
@@ -13,11 +40,11 @@ namespace {
 // per thread, the operands of X loaded before the transform, cos sigma read
 // from the installed field instead of computed. force_dS_dsigma, us, complex
 // slices with dense lines and a cosine per site -> this: 12^3 x 200 complex128
-// 11.8 -> 6.0 (bound by the host), 16^3 x 400, 8 rhs complex64 94 -> 55,
-// complex128 149 -> 118 (71 at 5.9 TB/s).
+// 11.8 -> 6.0 (bound by the host), 16^3 x 400, 8 rhs complex128 149 -> 118 (71 at
+// 5.9 TB/s).
 template <typename R, int NX>
 __global__ void __launch_bounds__(2 * NX * NX)
-    force_block_kernel(const C2<R>* __restrict__ X, const C2<R>* __restrict__ y, CoefPtr<R, NX> cf,
+    force_block_kernel(const C2<R>* __restrict__ X, const C2<R>* __restrict__ y, ForceT<R, NX> cf,
                        const double* __restrict__ cs, double A, int ntau, int nrhs,
                        double* __restrict__ grad) {
   constexpr int P = NX * NX, V = NX * NX * NX, RS = sizeof(R);
@@ -69,7 +96,11 @@ int launch_nx(const Lattice& L, const C2<R>* X, const C2<R>* y, int nrhs, double
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     attr = true;
   }
-  const CoefPtr<R, NX> cf{reinterpret_cast<const SplitCoef<R, NX>*>(fields<R>(L).split)};
+  ForceT<R, NX> cf;
+  if constexpr (sizeof(R) == 4)
+    cf.p = fields<R>(L).T;
+  else
+    cf.p = reinterpret_cast<const SplitCoef<R, NX>*>(fields<R>(L).split);
   hipLaunchKernelGGL((force_block_kernel<R, NX>), dim3((unsigned)L.ntau), dim3(2 * NX * NX), lds,
                      L.stream, X, y, cf, L.f64.cs, L.A, L.ntau, nrhs, grad);
   UFG_HIP(hipGetLastError());

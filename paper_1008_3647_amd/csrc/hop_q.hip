@@ -176,7 +176,14 @@ int launch_hop_q(const Lattice& L, const C2<R>* x, C2<R>* y, double2 alpha, doub
     case 8: return n < 2048 ? launch_q<R, 8, 4>(L, a) : launch_q<R, 8, 8>(L, a);
     case 10:
       return n <= 512 ? launch_q<R, 10, 2>(L, a) : launch_q<R, 10, sizeof(R) == 4 ? 5 : 6>(L, a);
-    case 12: return n <= 512 ? launch_q<R, 12, 2>(L, a) : launch_q<R, 12, 5>(L, a);
+    case 12:
+      // complex128: one workgroup per CU while that is enough (degree 8, us, two
+      // launches / G = 2 / G = 3: 110 slices, 3 rhs 128 / 140 / 95; 400, 1 rhs 131 / 141 /
+      // 98; 60, 8 rhs 139 / 145 / 105)
+      if constexpr (sizeof(R) == 8) {
+        if (n > 256 && n <= 512) return launch_q<R, 12, 3>(L, a);
+      }
+      return n <= 512 ? launch_q<R, 12, 2>(L, a) : launch_q<R, 12, 5>(L, a);
     case 14:
       if (sizeof(R) == 4 && n > 1024) return launch_q<R, 14, 4>(L, a);
       return launch_q<R, 14, 2>(L, a);

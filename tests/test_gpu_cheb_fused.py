@@ -22,7 +22,7 @@ TOL = {torch.complex128: 1e-12, torch.complex64: 2e-4}
 
 @pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
 @pytest.mark.parametrize("nx,ntau,nrhs", [
-    (8, 2, 1), (8, 3, 2), (8, 10, 3), (8, 2049, 1), (12, 2, 1), (12, 7, 3), (12, 514, 1),
+    (8, 2, 1), (8, 3, 2), (8, 10, 3), (8, 2049, 1), (12, 2, 1), (12, 7, 3), (12, 514, 1), (12, 259, 1), (12, 44, 6),
     (16, 2, 2), (16, 5, 1), (6, 2, 1), (6, 9, 2), (6, 2050, 1), (10, 4, 2), (10, 514, 1),
     (14, 3, 2), (14, 513, 1), (14, 1026, 1),
 ])

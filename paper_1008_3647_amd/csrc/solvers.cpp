@@ -183,7 +183,8 @@ int bicgstab_step(Lattice& L, const PcPlan& pc, int op, const C2<RO>* b, C2<RO>*
   // preconditioned operator Hermitian-like, where the limit only slows it.
   K.prm.limit_omega = (pc.kind == UFG_PC_NONE || pc.kind == UFG_PC_WCE) ? 1 : 0;
   UFG_TRY(L.flags.ensure(3 * nrhs));
-  K.mirror = L.flags.poll();
+  // read by the unfused form only (a write to host memory by every finalize)
+  if (need_pc || !stream_supported(L)) K.mirror = L.flags.poll();
   const int nvb = vec_blocks(L, nrhs);
   const int nhb = hop_blocks_per_rhs(L);
   const double2 one{1.0, 0.0}, zero{0.0, 0.0};

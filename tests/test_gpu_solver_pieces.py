@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from synthetic import sigma_field, gaussian_rhs
 from gpu_util import require_gpu, to_dev, to_host, say, TAU, G
 
@@ -45,3 +46,27 @@ def test_interval_in_pieces(check):
     _, st1 = L.solve_bicgstab(to_dev(b[:1]), "M", Precond("wce", wce_order=2), tol=1e-11,
                               check_every=check)
     assert st1["status"] == 0 and st1["iters"][0] > 1
+
+
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("check", [1, 4, 7, 9, 64])
+def test_fused_intervals(check, mixed):
+    """The unpreconditioned form on a streaming lattice: it keeps whole intervals at
+    every length. Converged (the oracle's residual), and FP64 counts whole intervals."""
+    require_gpu()
+    from paper_1008_3647_amd import Lattice
+    nx, ntau, tol = 8, 24, 1e-10
+    sigma = sigma_field(nx, ntau, 481)
+    b = gaussian_rhs(nx, ntau, [482, 483])
+    L = Lattice(nx, ntau, TAU, G, torch.complex128)
+    L.set_aux_field(to_dev(sigma))
+    for _ in range(2):
+        say(f"fused check_every={check} mixed={mixed}")
+        x, st = L.solve_bicgstab(to_dev(b), "M", tol=tol, mixed=mixed, check_every=check)
+        say(st)
+        assert st["status"] == 0
+        if not mixed:
+            assert st["mv"] == 2 * check * (-(-max(st["iters"]) // check))
+        for k in range(2):
+            r = oracle.apply_M(to_host(x)[k], sigma, TAU, G) - b[k]
+            assert np.linalg.norm(r) <= 1.2 * tol * np.linalg.norm(b[k])

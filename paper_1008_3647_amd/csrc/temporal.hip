@@ -9,6 +9,8 @@
 //     lattices without the block form of U (wce.hip has the others)
 // Consecutive threads take consecutive sites so every access along t is a
 // coalesced row.
+#include <cmath>
+
 #include "slice_t3.h"
 #include "ufg_internal.h"
 
@@ -57,14 +59,20 @@ __global__ void field_setup_kernel(const double* __restrict__ sigma, double* own
 // every chunk multiplies its 2 x 2 matrices (no division, no cancellation), the
 // products of the chunks before are applied to (E_0 = alpha, 1), and the
 // recursion as printed runs from there. Matrices and vectors are rescaled by
-// powers of two. Against long double over Ntau = 2..1000, alpha = 1..3: error
-// no larger than the recursion's from D_0 (alpha = 1, Ntau = 200: 4e-13 against
-// 4e-11, and equal where that is at rounding level).
+// powers of two by the lower row, which bounds the upper one (E <= alpha) but not the
+// other way round (alpha = 1 keeps the upper one at (1, 0) while the lower one is a
+// product of all q). Between chunks E is kept at 2^-54 alpha or more, the rounding of
+// the recursion's own term q / D: an E that is exact down to 2^-1000 would give factors
+// L whose products leave the range of complex64 where b^2 falls below 1 again.
+// Against 300 digits over Ntau = 200..4000, alpha = 1..3, tau g = 0.25..40: error no
+// larger than the recursion's from D_0 (alpha = 1, Ntau = 200: 3e-13 against 6e-11;
+// equal where that is at rounding level or, tau g = 1.1, lost altogether).
+// chunks = 1: the recursion as printed from D_0 alone, see launch_sca_setup.
 // The last workgroup instead writes the largest of the nblk partial maxima to
 // bmax_host (pinned host memory; none when null).
 constexpr int kSetupSites = 16, kSetupChunks = 32;
 __global__ void __launch_bounds__(kSetupSites* kSetupChunks)
-    sca_setup_kernel(const double* __restrict__ b, int V, int ntau, double alpha,
+    sca_setup_kernel(const double* __restrict__ b, int V, int ntau, double alpha, int chunks,
                      double* __restrict__ D64, double* __restrict__ L64, float* __restrict__ D32,
                      float* __restrict__ L32, const double* __restrict__ bmax_part, int nblk,
                      double* bmax_host) {
@@ -80,13 +88,16 @@ __global__ void __launch_bounds__(kSetupSites* kSetupChunks)
   const int ml = threadIdx.x % kSetupSites, c = threadIdx.x / kSetupSites;
   const int n = blockIdx.x * kSetupSites + ml;
   const bool act = n < V;
-  const int K = (ntau - 1 + kSetupChunks - 1) / kSetupChunks;  // steps t = 1 .. ntau - 1
+  const int K = (ntau - 1 + chunks - 1) / chunks;  // steps t = 1 .. ntau - 1
   const int s0 = min(1 + c * K, ntau), s1 = min(s0 + K, ntau);
   auto bat = [&](int t) -> double { return b[(long long)t * V + n]; };
-  auto scale_of = [](double v) -> int { return max(-1000, min(1000, -ilogb(v))); };
-  double m00 = 1.0, m01 = 0.0, m10 = 0.0, m11 = 1.0, b0 = 0.0;
-  if (act) {
-    b0 = bat(0);
+  // exponent that brings v to [1, 2); zero, infinity and NaN stay as they are
+  auto scale_of = [](double v) -> int {
+    return v > 0.0 && v < HUGE_VAL ? max(-1000, min(1000, -ilogb(v))) : 0;
+  };
+  double m00 = 1.0, m01 = 0.0, m10 = 0.0, m11 = 1.0;
+  const double b0 = act ? bat(0) : 0.0;
+  if (act && chunks > 1) {  // (the last chunk too: its b is then near for the recursion)
 #pragma unroll 8
     for (int t = s0; t < s1; ++t) {
       const double bp = bat(t - 1), q = bp * bp, f = (alpha - 1.0) * q;
@@ -96,7 +107,7 @@ __global__ void __launch_bounds__(kSetupSites* kSetupChunks)
       m00 = u0;
       m01 = u1;
       if (((t - s0) & 7) == 7) {
-        const int x = scale_of(fmax(fabs(m00), fabs(m01)));
+        const int x = scale_of(fmax(m10, m11));
         m00 = ldexp(m00, x);
         m01 = ldexp(m01, x);
         m10 = ldexp(m10, x);
@@ -110,7 +121,7 @@ __global__ void __launch_bounds__(kSetupSites* kSetupChunks)
   sm[3][c][ml] = m11;
   __syncthreads();
   if (!act) return;
-  const double D0 = alpha + b0 * b0;
+  const double D0 = alpha + b0 * b0, least = 0x1p-54 * alpha;
   double v0 = alpha, v1 = 1.0;
   for (int j = 0; j < c; ++j) {
     const double u0 = sm[0][j][ml] * v0 + sm[1][j][ml] * v1;
@@ -118,6 +129,7 @@ __global__ void __launch_bounds__(kSetupSites* kSetupChunks)
     const int x = scale_of(u1);
     v0 = ldexp(u0, x);
     v1 = ldexp(u1, x);
+    if (v0 < least) v0 = least;  // v1 is in [1, 2); a NaN stays
   }
   if (c == 0) {
     D64[n] = D0;
@@ -411,10 +423,18 @@ int launch_field_setup(Lattice& L, const double* sigma, double* bmax_part, int n
 
 int launch_sca_setup(Lattice& L, double alpha, const double* bmax_part, int nblk,
                      double* bmax_host) {
+  // In chunks where every term of the maps is positive and eight steps, each growing
+  // their entries by at most alpha + b^2, stay within the exponent's range.
+  // Otherwise one thread per site runs the recursion as printed: alpha < 1 (terms
+  // cancel, errors up to 15 times the recursion's) and magnitudes of no
+  // preconditioner in use (alpha above 1e33, or tau g above 75). 12^3 x 200: 10 us in
+  // chunks, 41 us so.
+  const double bm = 1.0 + std::fabs(L.A);
+  const int chunks = alpha >= 1.0 && alpha * (1.0 + bm * bm) < 0x1p110 ? kSetupChunks : 1;
   hipLaunchKernelGGL(sca_setup_kernel, dim3((L.V + kSetupSites - 1) / kSetupSites + (bmax_host ? 1 : 0)),
                      dim3(kSetupSites * kSetupChunks), 0,
-                     L.stream, L.f64.b, L.V, L.ntau, alpha, L.f64.scaD, L.f64.scaL, L.f32.scaD,
-                     L.f32.scaL, bmax_part, nblk, bmax_host);
+                     L.stream, L.f64.b, L.V, L.ntau, alpha, chunks, L.f64.scaD, L.f64.scaL,
+                     L.f32.scaD, L.f32.scaL, bmax_part, nblk, bmax_host);
   UFG_HIP(hipGetLastError());
   L.sca_alpha = alpha;
   return UFG_OK;

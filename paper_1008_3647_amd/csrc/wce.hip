@@ -383,11 +383,16 @@ __global__ void __launch_bounds__(MODES* CHUNKS)
 template <typename R, int MODES, int CHUNKS, int KEEP>
 int launch_scan_shape(const Lattice& L, R* carry, int slab, int nslab, int nrhs, bool adjoint,
                       const int* gate) {
-  hipLaunchKernelGGL((wce_scan_kernel<R, MODES, CHUNKS, KEEP>),
-                     dim3((unsigned)((L.V + MODES - 1) / MODES), (unsigned)(2 * nrhs)),
-                     dim3(MODES * CHUNKS), 0, L.stream, carry, L.f64.lam, L.V, L.ntau, slab, nslab,
-                     adjoint ? 1 : 0, gate);
-  UFG_HIP(hipGetLastError());
+  constexpr int kMost = 32767;  // right-hand sides a launch: grid.y ends at 65535
+  for (int r0 = 0; r0 < nrhs; r0 += kMost) {
+    hipLaunchKernelGGL((wce_scan_kernel<R, MODES, CHUNKS, KEEP>),
+                       dim3((unsigned)((L.V + MODES - 1) / MODES),
+                            (unsigned)(2 * std::min(kMost, nrhs - r0))),
+                       dim3(MODES * CHUNKS), 0, L.stream, carry + (long long)r0 * nslab * 2 * L.V,
+                       L.f64.lam, L.V, L.ntau, slab, nslab, adjoint ? 1 : 0,
+                       gate ? gate + r0 : nullptr);
+    UFG_HIP(hipGetLastError());
+  }
   return UFG_OK;
 }
 

@@ -406,22 +406,30 @@ int lattice_norm2_noalloc(ufg_lattice L, const void* x, int nrhs, double* out_de
 /*
  * lattice_tune -- launch parameters chosen by the autotuner (0 keeps the
  *   default): `slab` time slices per workgroup of the streaming M / M^T kernel
- *   and of the weak-coupling launches (Nx = 6 to 16; 1..Ntau), `vec_blocks`
- *   workgroups per right-hand side of the Krylov vector kernels (1..4096).
- *   Results do not depend on them beyond floating-point summation order.
+ *   (Nx = 6 to 16; 1..Ntau), `vec_blocks` workgroups per right-hand side of
+ *   the Krylov vector kernels (1..4096). Results do not depend on them beyond
+ *   floating-point summation order.
  */
 int lattice_tune(ufg_lattice L, int slab, int vec_blocks);
 
 /*
  * lattice_tune_slabs -- number of slabs per right-hand side of the streaming
- *   M / M^T kernel and of the weak-coupling launches (1..Ntau; 0 derives it
- *   from lattice_tune's slab as ceil(Ntau / slab)). Slab s covers slices
- *   [s Ntau / n, (s + 1) Ntau / n), so the count need not divide Ntau; it sets
- *   the grid (n x nrhs workgroups) to fit the number of resident workgroups
- *   (the weak-coupling launches take slabs of ceil(Ntau / n) slices). Same
- *   result guarantee as lattice_tune.
+ *   M / M^T kernel (1..Ntau; 0 derives it from lattice_tune's slab as
+ *   ceil(Ntau / slab)). Slab s covers slices [s Ntau / n, (s + 1) Ntau / n), so
+ *   the count need not divide Ntau; it sets the grid (n x nrhs workgroups) to fit
+ *   the number of resident workgroups. Same result guarantee as lattice_tune.
  */
 int lattice_tune_slabs(ufg_lattice L, int nslab);
+
+/*
+ * lattice_tune_wce -- time slices per workgroup of the weak-coupling launches
+ *   (dim = 3, Nx = 6 to 16; 1..Ntau; 0: the library's rule, by the number of
+ *   slices of all right-hand sides). They are a parameter of their own, which
+ *   lattice_tune does not touch: the operator runs best on slabs of one or a
+ *   few slices, these launches on longer ones. Same result guarantee as
+ *   lattice_tune.
+ */
+int lattice_tune_wce(ufg_lattice L, int slab);
 
 /*
  * lattice_tune_order -- workgroup numbering of the streaming M / M^T kernel.

@@ -94,6 +94,7 @@ _SIGNATURES = {
     "force_dS_dsigma": (C.c_int, [_P, _P, _P, C.c_int, _P]),
     "lattice_tune": (C.c_int, [_P, C.c_int, C.c_int]),
     "lattice_tune_slabs": (C.c_int, [_P, C.c_int]),
+    "lattice_tune_wce": (C.c_int, [_P, C.c_int]),
     "lattice_tune_order": (C.c_int, [_P, C.c_int, C.c_int]),
     "lattice_tune_transform": (C.c_int, [_P, C.c_int]),
     "precond_lam_max": (C.c_int, [_P, C.POINTER(ufg_precond), C.POINTER(C.c_double)]),

@@ -442,6 +442,15 @@ int lattice_tune_slabs(ufg_lattice h, int nslab) {
   return UFG_OK;
 }
 
+int lattice_tune_wce(ufg_lattice h, int slab) {
+  Lattice* L = check_handle(h);
+  UFG_CHECK(L != nullptr, "lattice_tune_wce: NULL handle");
+  UFG_CHECK(slab >= 0 && slab <= L->ntau, "lattice_tune_wce: slab must be 0..ntau");
+  UFG_HIP(hipStreamSynchronize(L->stream));
+  L->wce_slab = slab;
+  return UFG_OK;
+}
+
 int precond_lam_max(ufg_lattice h, const ufg_precond* p, double* out_host) {
   Lattice* L = check_handle(h);
   UFG_CHECK(L != nullptr, "precond_lam_max: NULL handle");

@@ -107,6 +107,7 @@ struct Lattice {
   std::vector<int> mode_perm;       // block-ordered mode -> column of U
   int slab = 0;                    // time slices per workgroup of the streaming kernel (0: default)
   int nslab = 0;                   // slabs per rhs of the streaming kernel (0: from slab)
+  int wce_slab = 0;                // time slices per workgroup of the weak-coupling launches (0: rule)
   int vec_blocks = 0;              // workgroups per rhs of the vector kernels (0: default)
   int xcd_group = -1;              // slab groups per XCD of the streaming kernels (-1: default)
   int xcd_rhs_inner = 0;           // 1: an XCD takes every rhs of a slab group in turn

@@ -495,8 +495,9 @@ int last_change(const Lattice& L, const WceArgs<R>& a, int nslab) {
 int wce_slab(const Lattice& L, int nrhs) {
   // the scan addresses one rhs's slab ends by 32-bit byte offsets: keep them below 2 GiB
   const int least = 1 + (int)(((long long)L.ntau * 2 * L.V * 8) >> 30);
-  if (L.nslab > 0) return std::max(least, (L.ntau + L.nslab - 1) / L.nslab);  // nslab <= ntau
-  if (L.slab > 0) return std::max(least, std::min(L.slab, L.ntau));
+  // Not the operator's slab, which is best at 1 there (453 us below): a lattice tuned
+  // for M took 462 us instead of 287 for order 2 at 16^3 x 400, 8 rhs complex64.
+  if (L.wce_slab > 0) return std::max(least, L.wce_slab);  // at most ntau
   // Longer slabs make the scan cheaper (its traffic is 1 / slab of a pass) and
   // each launch longer (a slab's slices run one after the other); with n slices
   // in all the balance lies near sqrt(n / 128). Order-2 application, us at slab

@@ -238,16 +238,19 @@ class Lattice:
                   maxit=maxit, mixed=bool(mixed))
         return x, stats
 
-    def tune(self, slab=0, vec_blocks=0, nslab=0, xcd_group=-1, rhs_inner=False, transform=0):
+    def tune(self, slab=0, vec_blocks=0, nslab=0, xcd_group=-1, rhs_inner=False, transform=0,
+             wce_slab=0):
         """Launch parameters (0 = library default, xcd_group -1 = default); see
-        lattice_tune, lattice_tune_slabs, lattice_tune_order and
-        lattice_tune_transform in ufg.h (nslab, when given, overrides slab)."""
+        lattice_tune, lattice_tune_slabs, lattice_tune_order,
+        lattice_tune_transform and lattice_tune_wce in ufg.h (nslab, when given,
+        overrides slab)."""
         L.check(self._lib.lattice_tune(self._h, int(slab), int(vec_blocks)), "lattice_tune")
         L.check(self._lib.lattice_tune_slabs(self._h, int(nslab)), "lattice_tune_slabs")
         L.check(self._lib.lattice_tune_order(self._h, int(xcd_group), int(bool(rhs_inner))),
                 "lattice_tune_order")
         L.check(self._lib.lattice_tune_transform(self._h, int(transform)),
                 "lattice_tune_transform")
+        L.check(self._lib.lattice_tune_wce(self._h, int(wce_slab)), "lattice_tune_wce")
 
     def _real_field(self, t, name):
         if not isinstance(t, torch.Tensor) or t.device.type != "cuda":

@@ -253,14 +253,29 @@ __global__ void __launch_bounds__(NX * NX, sizeof(R) == 8 && NX == 16 ? 2 : 1)
 #pragma unroll
   for (int z = 0; z < NX; ++z)
     U[z] = C2<R>{bload_real<R>(rc, vo, z * P * RS), bload_real<R>(rc, vo, (V + z * P) * RS)};
+  auto load = [&](int k, auto& Y) {
+    const int t = a.adjoint ? t1 - 1 - (k - t0) : k;
+    const auto rm = make_rsrc(a.modes + 2 * ((long long)r * ntau + t) * V, 2 * V * RS);
+#pragma unroll
+    for (int z = 0; z < NX; ++z)
+      Y[z] = C2<R>{bload_real<R>(rm, vo, z * P * RS), bload_real<R>(rm, vo, (V + z * P) * RS)};
+  };
+  // the next slice in flight as in FIRST (16^3 x 400, 8 rhs complex128: 132 -> 98 us, 16^3
+  // x 100, 4 rhs 25.2 -> 19.2); with the auxiliary term no difference (150 us)
+  constexpr bool kPre = !AUX && sizeof(R) == 8 && NX == 16;
+  C2<R> N[kPre ? NX : 1];
+  if constexpr (kPre) load(t0, N);
   for (int k = t0; k < t1; ++k) {
     const int t = a.adjoint ? t1 - 1 - (k - t0) : k;
     const long long o = ((long long)r * ntau + t) * V;
-    const auto rm = make_rsrc(a.modes + 2 * o, 2 * V * RS);
     C2<R> X[NX];
+    if constexpr (kPre) {
 #pragma unroll
-    for (int z = 0; z < NX; ++z)
-      X[z] = C2<R>{bload_real<R>(rm, vo, z * P * RS), bload_real<R>(rm, vo, (V + z * P) * RS)};
+      for (int z = 0; z < NX; ++z) X[z] = N[z];
+      if (k + 1 < t1) load(k + 1, N);
+    } else {
+      load(k, X);
+    }
 #pragma unroll
     for (int z = 0; z < NX; ++z) {
       const R lam = bload_real<R>(rl, vo, z * P * RS);

@@ -521,8 +521,21 @@ int wce_slab(const Lattice& L, int nrhs) {
   // complex128 180 / 148 / 144 / 153 / 180; 8^3 x 160, 4 rhs (640) 44 / 40 / 46 /
   // 48 / 64; 16^3 x 400, 1 rhs (400) complex64 89 / 81 / 96 / 108 / 150; 12^3 x
   // 200, 1 rhs (200) complex128 55 / 57 / 83 / 93 / 139.
-  const double n = (double)L.ntau * nrhs;
-  return std::max(least, std::min(8, (int)std::lround(std::sqrt(n / 128.0))));
+  const long long n = (long long)L.ntau * nrhs;
+  const int s = std::max(1, std::min(8, (int)std::lround(std::sqrt(n / 128.0))));
+  // From 3 on, a neighbour that leaves fewer slices to the CU with most workgroups
+  // (256 CUs; a longer slab for Nx of 12 and more only: 8^3 at n = 2400 prefers 4, 72 us,
+  // to 5, 76). us at slab 2 / 3 for n = 800: 16^3 complex64 order 0 / 2 39 / 44, 98 /
+  // 108, complex128 62 / 71, 177 / 191; 12^3 complex128 order 0 36 / 43; at 4 / 5 for n =
+  // 2400, 16^3 complex128 order 2 483 / 449.
+  auto most = [&](int k) {
+    const long long wg = (long long)((L.ntau + k - 1) / k) * nrhs;
+    return (wg + 255) / 256 * k;
+  };
+  int best = s;
+  for (int k : {s - 1, s + 1})
+    if (s >= 3 && k <= 8 && (k < s || L.nx >= 12) && most(k) < most(best)) best = k;
+  return std::max(least, best);
 }
 
 template <typename R>

@@ -44,7 +44,7 @@ enum PairEpi {
 
 template <typename R>
 struct WceArgs {
-  R* carry = nullptr;         // [nrhs][nslab][2][V]: in before a slab, out after it
+  R* carry = nullptr;         // [nrhs][nslab][2][V]: in before a slab, out after it; null: zero
   R* modes = nullptr;         // [nrhs][ntau][2][V]
   const R* lam = nullptr;     // mode eigenvalues [V]
   int subtract = 0;           // (1 - lam Z)^{-1} - 1 instead of (1 - lam Z)^{-1}
@@ -153,7 +153,7 @@ __global__ void __launch_bounds__(NX * NX, sizeof(R) == 8 && NX == 16 ? 2 : 1)
       bstore_real<R>(X[z].y, rd, l * RS, (V + z * P) * RS);
     }
   }
-  const auto rc = make_rsrc(a.carry + ((long long)r * nslab + sb) * 2 * V, 2 * V * RS);
+  const auto rc = make_rsrc(a.carry + ((long long)r * nslab + sb) * 2 * V, a.carry ? 2 * V * RS : 0);
 #pragma unroll
   for (int z = 0; z < NX; ++z) {
     bstore_real<R>(W[z].x, rc, l * RS, z * P * RS);
@@ -248,7 +248,7 @@ __global__ void __launch_bounds__(NX * NX, sizeof(R) == 8 && NX == 16 ? 2 : 1)
   constexpr int RS = sizeof(R), ES = sizeof(C2<R>);
   const int vo = threadIdx.x * RS;
   const auto rl = make_rsrc(a.lam, V * RS);
-  const auto rc = make_rsrc(a.carry + ((long long)r * nslab + sb) * 2 * V, 2 * V * RS);
+  const auto rc = make_rsrc(a.carry + ((long long)r * nslab + sb) * 2 * V, a.carry ? 2 * V * RS : 0);
   C2<R> U[NX];
 #pragma unroll
   for (int z = 0; z < NX; ++z)
@@ -326,7 +326,7 @@ __device__ __forceinline__ double ipow(double x, int n) {
 template <typename R, int MODES, int CHUNKS, int KEEP>
 __global__ void __launch_bounds__(MODES* CHUNKS)
     wce_scan_kernel(R* carry, const double* __restrict__ lam_mode, int V, int ntau, int slab,
-                    int nslab, int adjoint, const int* gate) {
+                    int nslab, int adjoint, int inclusive, const int* gate) {
   __shared__ double cend[CHUNKS][MODES];
   __shared__ double cpow[CHUNKS][MODES];
   constexpr int RS = sizeof(R);
@@ -382,22 +382,22 @@ __global__ void __launch_bounds__(MODES* CHUNKS)
   v -= pv * U / (1.0 + lamN);  // U_{-1} = -U / (1 + lam^Ntau), carried to chunk c
 #pragma unroll
   for (int i = 0; i < KEEP; ++i) {
-    bstore_real<R>(R(v), rc, at(k0 + i), 0);
-    const double p = k0 + i == short_k ? lamL : lamS;
-    v = double(G[i]) + p * v;
+    const double p = k0 + i == short_k ? lamL : lamS, u = double(G[i]) + p * v;
+    bstore_real<R>(R(inclusive ? u : v), rc, at(k0 + i), 0);
+    v = u;
   }
 #pragma unroll 4
   for (int k = k0 + KEEP; k < k1; ++k) {
     const R g = bload_real<R>(rc, at(k), 0);
-    const double p = k == short_k ? lamL : lamS;
-    bstore_real<R>(R(v), rc, at(k), 0);
-    v = double(g) + p * v;
+    const double p = k == short_k ? lamL : lamS, u = double(g) + p * v;
+    bstore_real<R>(R(inclusive ? u : v), rc, at(k), 0);
+    v = u;
   }
 }
 
 template <typename R, int MODES, int CHUNKS, int KEEP>
 int launch_scan_shape(const Lattice& L, R* carry, int slab, int nslab, int nrhs, bool adjoint,
-                      const int* gate) {
+                      bool inclusive, const int* gate) {
   constexpr int kMost = 32767;  // right-hand sides a launch: grid.y ends at 65535
   for (int r0 = 0; r0 < nrhs; r0 += kMost) {
     hipLaunchKernelGGL((wce_scan_kernel<R, MODES, CHUNKS, KEEP>),
@@ -405,7 +405,7 @@ int launch_scan_shape(const Lattice& L, R* carry, int slab, int nslab, int nrhs,
                             (unsigned)(2 * std::min(kMost, nrhs - r0))),
                        dim3(MODES * CHUNKS), 0, L.stream, carry + (long long)r0 * nslab * 2 * L.V,
                        L.f64.lam, L.V, L.ntau, slab, nslab, adjoint ? 1 : 0,
-                       gate ? gate + r0 : nullptr);
+                       inclusive ? 1 : 0, gate ? gate + r0 : nullptr);
     UFG_HIP(hipGetLastError());
   }
   return UFG_OK;
@@ -413,17 +413,17 @@ int launch_scan_shape(const Lattice& L, R* carry, int slab, int nslab, int nrhs,
 
 template <typename R>
 int launch_scan(const Lattice& L, R* carry, int slab, int nslab, int nrhs, bool adjoint,
-                const int* gate) {
+                bool inclusive, const int* gate) {
   // Many columns: wide rows, short chunks. Few: 16 modes a row to have more
   // workgroups, and chunks that fit the registers. Order-2 application, us, with
   // 32 x 8 keeping 8 / 16 x 8 keeping 16 / 16 x 16 keeping 16: 16^3 x 400, 8 rhs (80
   // slabs) complex64 274 / 293 / 285 (32 x 16); 8^3 x 160, 4 rhs (80 slabs) 42.0 / 39.8 /
   // 41.3; 6^3 x 50 (50) 20.9 / 21.1 / 23.4; 12^3 x 200 (200) 65.5 / 58.6 / 53.0.
   if (2ll * L.V * nrhs >= 64 * 256)
-    return launch_scan_shape<R, 32, 8, 8>(L, carry, slab, nslab, nrhs, adjoint, gate);
+    return launch_scan_shape<R, 32, 8, 8>(L, carry, slab, nslab, nrhs, adjoint, inclusive, gate);
   if (nslab <= 128)
-    return launch_scan_shape<R, 16, 8, 16>(L, carry, slab, nslab, nrhs, adjoint, gate);
-  return launch_scan_shape<R, 16, 16, 16>(L, carry, slab, nslab, nrhs, adjoint, gate);
+    return launch_scan_shape<R, 16, 8, 16>(L, carry, slab, nslab, nrhs, adjoint, inclusive, gate);
+  return launch_scan_shape<R, 16, 16, 16>(L, carry, slab, nslab, nrhs, adjoint, inclusive, gate);
 }
 
 // The blocks of U^T and U, adjacent on the device.
@@ -507,7 +507,18 @@ int last_change(const Lattice& L, const WceArgs<R>& a, int nslab) {
 
 }  // namespace
 
-int wce_slab(const Lattice& L, int nrhs) {
+// With one slice a slab the slab ends are the modes themselves, and at order 0 nothing
+// but (1 - lam Z)^{-1} is wanted of them: the scan turns the modes into it in place, and
+// FIRST and LAST leave the carry out. Order 0 on 16^3 x 100, 4 rhs complex128: 43 us with
+// a carry at one or two slices a slab, 39 so; 60 slices, 8 rhs 47 / 42. For Nx = 16
+// only, and complex64 only beyond 512 slices (70 slices, 8 rhs 35 -> 33): where FIRST and
+// LAST are short the scan of the modes, whose lines FIRST has just spread over the XCDs'
+// L2s, takes longer than that of a carry (16^3 x 100, 4 rhs complex64 8.4 -> 11.6 us).
+static bool wce_direct(const Lattice& L, long long n, int order, bool fp64, int slab) {
+  return order == 0 && L.nx == 16 && slab == 1 && (fp64 || n > 512);
+}
+
+int wce_slab(const Lattice& L, int nrhs, int order, bool fp64) {
   // the scan addresses one rhs's slab ends by 32-bit byte offsets: keep them below 2 GiB
   const int least = 1 + (int)(((long long)L.ntau * 2 * L.V * 8) >> 30);
   // Not the operator's slab, which is best at 1 there (453 us below): a lattice tuned
@@ -522,6 +533,7 @@ int wce_slab(const Lattice& L, int nrhs) {
   // 48 / 64; 16^3 x 400, 1 rhs (400) complex64 89 / 81 / 96 / 108 / 150; 12^3 x
   // 200, 1 rhs (200) complex128 55 / 57 / 83 / 93 / 139.
   const long long n = (long long)L.ntau * nrhs;
+  if (wce_direct(L, n, order, fp64, 1) && n <= 600) return least;
   const int s = std::max(1, std::min(8, (int)std::lround(std::sqrt(n / 128.0))));
   // From 3 on, a neighbour that leaves fewer slices to the CU with most workgroups
   // (256 CUs; a longer slab for Nx of 12 and more only: 8^3 at n = 2400 prefers 4, 72 us,
@@ -547,9 +559,12 @@ int wce_modes_apply(Lattice& L, const PcPlan& pc, bool adjoint, const C2<R>* x, 
   WceArgs<R> a;
   a.modes = reinterpret_cast<R*>(slot_vec<R>(L, SLOT_PC0 + 0, nrhs, &rc));
   UFG_TRY(rc);
-  // one slice per slab: at most a vector
-  a.carry = reinterpret_cast<R*>(slot_vec<R>(L, SLOT_PC0 + 1, nrhs, &rc));
-  UFG_TRY(rc);
+  a.slab = wce_slab(L, nrhs, d, sizeof(R) == 8);
+  const bool direct = wce_direct(L, (long long)L.ntau * nrhs, d, sizeof(R) == 8, a.slab);
+  if (!direct) {  // one slice per slab: at most a vector
+    a.carry = reinterpret_cast<R*>(slot_vec<R>(L, SLOT_PC0 + 1, nrhs, &rc));
+    UFG_TRY(rc);
+  }
   R* u0 = nullptr;
   if (!adjoint && d > 0) {
     u0 = reinterpret_cast<R*>(slot_vec<R>(L, SLOT_PC0 + 2, nrhs, &rc));
@@ -558,13 +573,12 @@ int wce_modes_apply(Lattice& L, const PcPlan& pc, bool adjoint, const C2<R>* x, 
   a.lam = F.lam;
   a.field = F.sn;
   a.nrhs = nrhs;
-  a.slab = wce_slab(L, nrhs);
   a.adjoint = adjoint ? 1 : 0;
   a.gate = gate;
   const int nslab = (L.ntau + a.slab - 1) / a.slab;
   auto scan = [&]() -> int {
     cnt->m0inv += 1;
-    return launch_scan<R>(L, a.carry, a.slab, nslab, nrhs, adjoint, gate);
+    return launch_scan<R>(L, direct ? a.modes : a.carry, a.slab, nslab, nrhs, adjoint, direct, gate);
   };
   a.src = x;
   if (src) {

@@ -27,7 +27,8 @@ struct KrylovState {
   double* part = nullptr;   // [nrhs][nblk][4] (8 per block for the streaming reduction mode 4)
   double* part2 = nullptr;  // [nrhs][vector blocks][4]: partials kept across one operator launch
   double* part3 = nullptr;  // [nrhs][operator blocks][4]: partials read by the next operator launch
-  int* mirror = nullptr;    // [nrhs] pinned host copy of `active` kept by k_finalize (may be null)
+  int* mirror = nullptr;    // [nrhs] pinned host copy of `active`: k_finalize stores its changes
+                            // (null: none; the owner writes the first values)
   KrylovParams prm{};
 };
 

@@ -183,8 +183,6 @@ int bicgstab_step(Lattice& L, const PcPlan& pc, int op, const C2<RO>* b, C2<RO>*
   // preconditioned operator Hermitian-like, where the limit only slows it.
   K.prm.limit_omega = (pc.kind == UFG_PC_NONE || pc.kind == UFG_PC_WCE) ? 1 : 0;
   UFG_TRY(L.flags.ensure(3 * nrhs));
-  // read by the unfused form only (a write to host memory by every finalize)
-  if (need_pc || !stream_supported(L)) K.mirror = L.flags.poll();
   const int nvb = vec_blocks(L, nrhs);
   const int nhb = hop_blocks_per_rhs(L);
   const double2 one{1.0, 0.0}, zero{0.0, 0.0};
@@ -276,7 +274,7 @@ int bicgstab_step(Lattice& L, const PcPlan& pc, int op, const C2<RO>* b, C2<RO>*
   int cur = 0;          // P2[cur], V2[cur] hold the current p and v
   bool merged = false;  // p was formed by the merged x, r, p update
   // one iteration of the unfused form (preconditioned, or a lattice without
-  // the streaming kernel); whole check intervals of it replay from a graph
+  // the streaming kernel); pieces of check intervals replay from a graph of it
   // a weak-coupling preconditioner forms p and s in its first basis change
   const bool fuse_src = need_pc && pc_fuses_source(L, pc, op);
   auto classic_iteration = [&]() -> int {
@@ -322,10 +320,11 @@ int bicgstab_step(Lattice& L, const PcPlan& pc, int op, const C2<RO>* b, C2<RO>*
   // nothing (every rhs is inactive by then). The unfused form issues its
   // intervals in pieces of a few iterations and has one piece queued whenever
   // it waits: it reads a check point's flags behind the first piece of the next
-  // interval, and the active flags, which the finalize kernels keep in pinned
-  // memory, behind every other one, and leaves out the rest of an interval
+  // interval, and the active flags, whose changes the finalize kernels store to
+  // pinned memory, behind every other one, and leaves out the rest of an interval
   // once every rhs has stopped (a launch that does nothing still takes 2.5 us: a
-  // weak-coupling solve of 22 iterations at 12^3 x 200 issued 39).
+  // weak-coupling solve of 22 iterations at 12^3 x 200 issued 39). Counted as
+  // issued are whole intervals all the same, whatever their pieces.
   int posted = 0;
   Counters at_prev_post;  // the counters when the previous flags were posted
   auto all_idle = [&](const volatile int* f) {
@@ -334,7 +333,17 @@ int bicgstab_step(Lattice& L, const PcPlan& pc, int op, const C2<RO>* b, C2<RO>*
     return true;
   };
   IntervalGraph G;
-  const int piece = std::min(check, need_pc ? 2 : 5);
+  // Iterations a piece: a graph launch with its event costs about 5 us against
+  // iterations of 100 us with the weak-coupling launches, which converge in a few
+  // tens, and of 35 us without a preconditioner, which take hundreds. us an iteration
+  // at 2 / 5 / 10, check_every 10 (whole intervals, the host a check point behind): order 0 on
+  // 2D 8 x 200, 4 rhs 79.6 / 77.0 / 77.5 (76.6), 1D 8 x 400, 2 rhs 102.7 / 100.0 / 100.0
+  // (100.2); no preconditioner, 4^3 x 50 - / 34.8 / 33.7 (33.4). 12^3 x 200 order 2: HMC 24.8 ms at 2.
+  const int piece = std::min(check, need_pc ? (stream_supported(L) ? 2 : 5) : 10);
+  if (!fused && piece < check) {
+    K.mirror = L.flags.poll();
+    std::copy(hflags.begin(), hflags.begin() + nrhs, K.mirror);
+  }
   Counters per_it;  // what one iteration adds to the counters
   int pieces = 0;
   auto classic_interval = [&](int len) -> int {
@@ -356,7 +365,7 @@ int bicgstab_step(Lattice& L, const PcPlan& pc, int op, const C2<RO>* b, C2<RO>*
           per_it = Counters{cnt->mv - c0.mv, cnt->m0inv - c0.m0inv, cnt->sca - c0.sca};
         }
       }
-      UFG_HIP(hipEventRecord(L.flags.ev[2 + (pieces & 1)], L.stream));
+      if (K.mirror) UFG_HIP(hipEventRecord(L.flags.ev[2 + (pieces & 1)], L.stream));
       ++pieces;
       if (k == 0) {
         if (posted > 0) {  // the check point this interval follows

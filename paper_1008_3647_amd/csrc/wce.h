@@ -13,6 +13,6 @@ int wce_modes_apply(Lattice& L, const PcPlan& pc, bool adjoint, const C2<R>* x, 
                     int nrhs, const int* gate, Counters* cnt, const PcSource<R>* src);
 
 // Time slices per workgroup of those launches.
-int wce_slab(const Lattice& L, int nrhs, int order, bool fp64);
+int wce_slab(const Lattice& L, int nrhs, int order, bool fp64, bool fused_source);
 
 }  // namespace ufg

@@ -79,9 +79,14 @@ __device__ __forceinline__ void wce_item(int ncol, int& c, int& sb) {
   sb = lid / ncol;
 }
 
-// U^3T x per slice, and the slab's recurrence from zero.
-template <typename R, int NX, int SRC>
-__global__ void __launch_bounds__(NX * NX, sizeof(R) == 8 && NX == 16 ? 2 : 1)
+// U^3T x per slice, and the slab's recurrence from zero. AHEAD: the next slice's
+// operands in flight during the transform, for FP64 slices of Nx = 16 only, two
+// workgroups of which fill a CU's LDS (16^3 x 400, 8 rhs: 103 -> 87 us; complex64 57 -> 56
+// us, Nx = 12 slower by the registers it takes). With a fused source they take 302 and 366
+// registers, one workgroup per CU, and still gain where a slab has a next slice: 16^3 x
+// 100, 4 rhs (slabs of 2) 38.8 / 41.2 (SRC 1 / 2) -> 32.0 / 28.4 us, 400 slices 128 / 119 -> 127 / 110.
+template <typename R, int NX, int SRC, bool AHEAD>
+__global__ void __launch_bounds__(NX * NX, sizeof(R) == 8 && NX == 16 && !(SRC && AHEAD) ? 2 : 1)
     wce_first_kernel(WceArgs<R> a, CoefPtr<R, NX> cf, int ntau, int nslab) {
   constexpr int P = NX * NX, V = NX * NX * NX;
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -98,47 +103,51 @@ __global__ void __launch_bounds__(NX * NX, sizeof(R) == 8 && NX == 16 ? 2 : 1)
 #pragma unroll
   for (int z = 0; z < NX; ++z) W[z] = zero_of<C2<R>>();
   constexpr int ES = sizeof(C2<R>);
-  auto load = [&](int k, auto& Y) {
-    const int t = a.adjoint ? t1 - 1 - (k - t0) : k;
-    const auto rs = make_rsrc(a.src + ((long long)r * ntau + t) * V, V * ES);
-#pragma unroll
-    for (int z = 0; z < NX; ++z) Y[z] = bload<R>(rs, l * ES, z * P * ES);
+  // element z of a slice at offset o: x, or r, v and, for SRC 1, p
+  struct Operands {
+    C2<R> x, v, p;
   };
-  // the next slice in flight during the transform, for FP64 slices of Nx = 16
-  // only, two workgroups of which fill a CU's LDS (16^3 x 400, 8 rhs: 103 -> 87
-  // us; complex64 57 -> 56 us, Nx = 12 slower by the registers it takes)
-  constexpr bool kPre = SRC == 0 && sizeof(R) == 8 && NX == 16;
-  C2<R> N[kPre ? NX : 1];
-  if constexpr (kPre) load(t0, N);
-  for (int k = t0; k < t1; ++k) {
-    const int t = a.adjoint ? t1 - 1 - (k - t0) : k;
-    const long long o = ((long long)r * ntau + t) * V;
-    C2<R> X[NX];
-    if constexpr (kPre) {
-#pragma unroll
-      for (int z = 0; z < NX; ++z) X[z] = N[z];
-      if (k + 1 < t1) load(k + 1, N);
-    } else if constexpr (SRC == 0) {
-      load(k, X);
+  auto load = [&](long long o, int z) {
+    Operands e;
+    e.x = bload<R>(make_rsrc((SRC ? a.fr : a.src) + o, V * ES), l * ES, z * P * ES);
+    if constexpr (SRC != 0) e.v = bload<R>(make_rsrc(a.fv + o, V * ES), l * ES, z * P * ES);
+    if constexpr (SRC == 1) e.p = bload<R>(make_rsrc(a.fp + o, V * ES), l * ES, z * P * ES);
+    return e;
+  };
+  auto form = [&](const Operands& e) {
+    if constexpr (SRC == 1) {
+      const R dx = e.p.x - (q.wr * e.v.x - q.wi * e.v.y);
+      const R dy = e.p.y - (q.wr * e.v.y + q.wi * e.v.x);
+      return C2<R>{e.x.x + q.br * dx - q.bi * dy, e.x.y + q.br * dy + q.bi * dx};
+    } else if constexpr (SRC == 2) {
+      return C2<R>{e.x.x - (q.ar * e.v.x - q.ai * e.v.y), e.x.y - (q.ar * e.v.y + q.ai * e.v.x)};
     } else {
-      const auto rr = make_rsrc(a.fr + o, V * ES), rv = make_rsrc(a.fv + o, V * ES);
-      const auto rp = make_rsrc(SRC == 1 ? a.fp + o : nullptr, V * ES);
+      return e.x;
+    }
+  };
+  auto offset = [&](int k) {
+    return ((long long)r * ntau + (a.adjoint ? t1 - 1 - (k - t0) : k)) * V;
+  };
+  Operands N[AHEAD ? NX : 1];
+  if constexpr (AHEAD) {
+#pragma unroll
+    for (int z = 0; z < NX; ++z) N[z] = load(offset(t0), z);
+  }
+  for (int k = t0; k < t1; ++k) {
+    const long long o = offset(k);
+    C2<R> X[NX];
+#pragma unroll
+    for (int z = 0; z < NX; ++z) X[z] = form(AHEAD ? N[AHEAD ? z : 0] : load(o, z));
+    if constexpr (SRC != 0) {
       const auto rn = make_rsrc(a.fpnew + o, V * ES);
 #pragma unroll
-      for (int z = 0; z < NX; ++z) {
-        const int so = z * P * ES;
-        const C2<R> r0 = bload<R>(rr, l * ES, so), v0 = bload<R>(rv, l * ES, so);
-        if constexpr (SRC == 1) {
-          const C2<R> p0 = bload<R>(rp, l * ES, so);
-          const R dx = p0.x - (q.wr * v0.x - q.wi * v0.y);
-          const R dy = p0.y - (q.wr * v0.y + q.wi * v0.x);
-          X[z] = C2<R>{r0.x + q.br * dx - q.bi * dy, r0.y + q.br * dy + q.bi * dx};
-        } else {
-          X[z] = C2<R>{r0.x - (q.ar * v0.x - q.ai * v0.y), r0.y - (q.ar * v0.y + q.ai * v0.x)};
-        }
-      }
-#pragma unroll
       for (int z = 0; z < NX; ++z) bstore<R, false>(X[z], a.fpnew + o, rn, l * ES, z * P * ES);
+    }
+    if constexpr (AHEAD) {
+      if (k + 1 < t1) {
+#pragma unroll
+        for (int z = 0; z < NX; ++z) N[z] = load(offset(k + 1), z);
+      }
     }
     slice_T3<R, NX, 1>(cf, lds, l, X);
     const auto rd = make_rsrc(a.modes + 2 * o, 2 * V * RS);
@@ -452,10 +461,18 @@ CoefPtr<R, NX> coef_bwd(const Lattice& L) {
     return UFG_OK;                                                                             \
   } while (0)
 
+template <typename R, int NX, int SRC, bool AHEAD>
+int launch_first_kernel(const Lattice& L, const WceArgs<R>& a, int nslab) {
+  WCE_LAUNCH((wce_first_kernel<R, NX, SRC, AHEAD>), sizeof(C2<R>), nslab * a.nrhs, a,
+             (coef_fwd<R, NX>(L)));
+}
 template <typename R, int NX, int SRC>
 int launch_first(const Lattice& L, const WceArgs<R>& a, int nslab) {
-  WCE_LAUNCH((wce_first_kernel<R, NX, SRC>), sizeof(C2<R>), nslab * a.nrhs, a,
-             (coef_fwd<R, NX>(L)));
+  constexpr bool kAhead = sizeof(R) == 8 && NX == 16;
+  if constexpr (SRC != 0 && kAhead) {
+    if (a.slab == 1) return launch_first_kernel<R, NX, SRC, false>(L, a, nslab);
+  }
+  return launch_first_kernel<R, NX, SRC, kAhead>(L, a, nslab);
 }
 template <typename R, int NX, int EPI>
 int launch_pair(const Lattice& L, const WceArgs<R>& a, int nslab) {
@@ -518,7 +535,7 @@ static bool wce_direct(const Lattice& L, long long n, int order, bool fp64, int 
   return order == 0 && L.nx == 16 && slab == 1 && (fp64 || n > 512);
 }
 
-int wce_slab(const Lattice& L, int nrhs, int order, bool fp64) {
+int wce_slab(const Lattice& L, int nrhs, int order, bool fp64, bool fused_source) {
   // the scan addresses one rhs's slab ends by 32-bit byte offsets: keep them below 2 GiB
   const int least = 1 + (int)(((long long)L.ntau * 2 * L.V * 8) >> 30);
   // Not the operator's slab, which is best at 1 there (453 us below): a lattice tuned
@@ -534,6 +551,11 @@ int wce_slab(const Lattice& L, int nrhs, int order, bool fp64) {
   // 200, 1 rhs (200) complex128 55 / 57 / 83 / 93 / 139.
   const long long n = (long long)L.ntau * nrhs;
   if (wce_direct(L, n, order, fp64, 1) && n <= 600) return least;
+  // A FIRST that also forms its source is bound by its traffic, and slabs of two leave
+  // CUs without a workgroup below 512 slices. BiCGStab with order 0, us an iteration at slab 1 / 2:
+  // FP32-refined 16^3 x 100, 4 rhs 146 / 158, 60 slices, 8 rhs 156 / 171, 12^3 x 100, 4 rhs
+  // 104 / 109; FP64 12^3 121 / 128, 10^3 101 / 108, 6^3 64 / 67.
+  if (fused_source && order == 0 && n <= 512) return least;
   const int s = std::max(1, std::min(8, (int)std::lround(std::sqrt(n / 128.0))));
   // From 3 on, a neighbour that leaves fewer slices to the CU with most workgroups
   // (256 CUs; a longer slab for Nx of 12 and more only: 8^3 at n = 2400 prefers 4, 72 us,
@@ -559,7 +581,7 @@ int wce_modes_apply(Lattice& L, const PcPlan& pc, bool adjoint, const C2<R>* x, 
   WceArgs<R> a;
   a.modes = reinterpret_cast<R*>(slot_vec<R>(L, SLOT_PC0 + 0, nrhs, &rc));
   UFG_TRY(rc);
-  a.slab = wce_slab(L, nrhs, d, sizeof(R) == 8);
+  a.slab = wce_slab(L, nrhs, d, sizeof(R) == 8, src != nullptr);
   const bool direct = wce_direct(L, (long long)L.ntau * nrhs, d, sizeof(R) == 8, a.slab);
   if (!direct) {  // one slice per slab: at most a vector
     a.carry = reinterpret_cast<R*>(slot_vec<R>(L, SLOT_PC0 + 1, nrhs, &rc));

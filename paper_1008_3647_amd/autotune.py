@@ -58,8 +58,14 @@ def _store(path, data):
         pass
 
 
+def streaming(L: Lattice):
+    """Whether M and M^T of this lattice run in the streaming kernels, which the
+    slab and the numbering act on (csrc: stream_supported)."""
+    return L.dim == 3 and L.nx >= 6 and L.ntau * L.nx ** 3 * 16 < 2 ** 31
+
+
 def candidate_slabs(L: Lattice):
-    if L.nx not in (8, 12, 16):
+    if not streaming(L):
         return [0]
     return [s for s in (1, 2, 3, 4, 6, 8) if s <= L.ntau]
 
@@ -67,6 +73,14 @@ def candidate_slabs(L: Lattice):
 # workgroup numberings of the streaming kernels: (xcd_group, rhs_inner);
 # (0, False) is the contiguous per-XCD numbering (see lattice_tune_order)
 ORDERS = ((0, False), (5, False), (10, False), (5, True), (10, True))
+
+
+def candidate_orders(L: Lattice, orders=ORDERS):
+    """`orders` whose groups fit the time extent, or the library's default alone
+    where the numbering acts on nothing."""
+    if not streaming(L):
+        return ((-1, False),)
+    return tuple(o for o in orders if o[0] <= L.ntau)
 
 
 def _time_solve(L, b, op, precond, mixed, iters, reps):
@@ -86,8 +100,8 @@ def tune(L: Lattice, b: torch.Tensor, mixed=False, op="M", iters=16, reps=2,
          vec_blocks=(0, 32, 64, 128, 256, 512), orders=ORDERS,
          cache: str | None = DEFAULT_CACHE, force=False, verbose=False, precond=None,
          finalists=3, refine_iters=100, refine_reps=2):
-    """Pick the launch shape for solves of `b` on `L` (with `precond`, whose
-    basis-change launches follow the same slab choice): slices per slab and
+    """Pick the launch shape for solves of `b` on `L` (with `precond`; the
+    weak-coupling launches keep the slab of their own rule): slices per slab and
     workgroup numbering of the streaming kernels first (vector kernels at their
     default), then the workgroups per rhs of the vector kernels for that
     choice; the `finalists` fastest of all are timed again over
@@ -95,7 +109,7 @@ def tune(L: Lattice, b: torch.Tensor, mixed=False, op="M", iters=16, reps=2,
     cannot separate shapes a few tenths of a per cent apart). Returns a dict
     with the choice and the timings of every candidate."""
     nrhs = b.shape[0]
-    key = "v3|" + _key(L, nrhs, mixed, precond)
+    key = "v4|" + _key(L, nrhs, mixed, precond)  # v3: of earlier kernels
     data = _load(cache) if cache else {}
     if not force and key in data:
         best = data[key]
@@ -113,9 +127,8 @@ def tune(L: Lattice, b: torch.Tensor, mixed=False, op="M", iters=16, reps=2,
                   f"{t * 1e3:.2f} ms", flush=True)
         return results[-1]
 
-    streaming = L.nx in (8, 12, 16)
     for slab in candidate_slabs(L):
-        for grp, ri in (orders if streaming else ((0, False),)):
+        for grp, ri in candidate_orders(L, orders):
             run(slab, 0, grp, ri)
     first = min(results, key=lambda d: d["seconds"])
     for vb in vec_blocks:
@@ -169,10 +182,9 @@ def tune_apply(L: Lattice, x, dagger=False, launches=100, reps=3, orders=ORDERS,
     x = xs[0]
     if transforms is None:
         transforms = (0, 1, 2) if (x.dtype == torch.complex64 and L.nx == 16) else (0,)
-    streaming = L.nx in (8, 12, 16)
     results = []
     for slab in candidate_slabs(L):
-        for grp, ri in (orders if streaming else ((0, False),)):
+        for grp, ri in candidate_orders(L, orders):
             for tr in transforms:
                 L.tune(slab, 0, xcd_group=grp, rhs_inner=ri, transform=tr)
                 for i in range(len(xs)):  # warm-up

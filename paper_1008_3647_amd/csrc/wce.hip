@@ -44,7 +44,7 @@ enum PairEpi {
 
 template <typename R>
 struct WceArgs {
-  R* carry = nullptr;         // [nrhs][nslab][2][V]: in before a slab, out after it; null: zero
+  R* carry = nullptr;         // [nrhs][nslab][2][V]: in before a slab, out after it; null: none
   R* modes = nullptr;         // [nrhs][ntau][2][V]
   const R* lam = nullptr;     // mode eigenvalues [V]
   int subtract = 0;           // (1 - lam Z)^{-1} - 1 instead of (1 - lam Z)^{-1}
@@ -162,7 +162,8 @@ __global__ void __launch_bounds__(NX * NX, sizeof(R) == 8 && NX == 16 && !(SRC &
       bstore_real<R>(X[z].y, rd, l * RS, (V + z * P) * RS);
     }
   }
-  const auto rc = make_rsrc(a.carry + ((long long)r * nslab + sb) * 2 * V, a.carry ? 2 * V * RS : 0);
+  if (!a.carry) return;
+  const auto rc = make_rsrc(a.carry + ((long long)r * nslab + sb) * 2 * V, 2 * V * RS);
 #pragma unroll
   for (int z = 0; z < NX; ++z) {
     bstore_real<R>(W[z].x, rc, l * RS, z * P * RS);
@@ -257,11 +258,15 @@ __global__ void __launch_bounds__(NX * NX, sizeof(R) == 8 && NX == 16 ? 2 : 1)
   constexpr int RS = sizeof(R), ES = sizeof(C2<R>);
   const int vo = threadIdx.x * RS;
   const auto rl = make_rsrc(a.lam, V * RS);
-  const auto rc = make_rsrc(a.carry + ((long long)r * nslab + sb) * 2 * V, a.carry ? 2 * V * RS : 0);
   C2<R> U[NX];
 #pragma unroll
-  for (int z = 0; z < NX; ++z)
-    U[z] = C2<R>{bload_real<R>(rc, vo, z * P * RS), bload_real<R>(rc, vo, (V + z * P) * RS)};
+  for (int z = 0; z < NX; ++z) U[z] = zero_of<C2<R>>();
+  if (a.carry) {
+    const auto rc = make_rsrc(a.carry + ((long long)r * nslab + sb) * 2 * V, 2 * V * RS);
+#pragma unroll
+    for (int z = 0; z < NX; ++z)
+      U[z] = C2<R>{bload_real<R>(rc, vo, z * P * RS), bload_real<R>(rc, vo, (V + z * P) * RS)};
+  }
   auto load = [&](int k, auto& Y) {
     const int t = a.adjoint ? t1 - 1 - (k - t0) : k;
     const auto rm = make_rsrc(a.modes + 2 * ((long long)r * ntau + t) * V, 2 * V * RS);

@@ -104,13 +104,18 @@ typedef struct {
  *   delta      reliable-update trigger: update when the inner residual has
  *              fallen below delta times its maximum since the last update.
  *   check_every  iterations between check points (>= 1). Reliable updates
- *              and restarts happen at check points. The host reads the flags
- *              of a check point at the next one (it never waits for the device
- *              there), so a solve ends up to two intervals after convergence
- *              on launches that do no work (not counted in the statistics).
- *   eager      0: where the iteration is not fused into the streaming kernel
- *              (preconditioned solves, CG, Nx = 2 and 4), every
- *              check interval after the first replays a HIP graph captured
+ *              and restarts happen at check points. Where BiCGStab is fused into
+ *              the streaming kernel (no preconditioner, dim = 3, Nx of 6 and more)
+ *              and in CG, the host reads the flags of a check point at the next
+ *              one (it waits for nothing else), so a solve ends up to two
+ *              intervals after convergence on launches that do no work. Every
+ *              other BiCGStab is issued in pieces of two iterations (dim = 3, Nx of
+ *              6 and more), five or, without a preconditioner, ten, the host one
+ *              piece ahead of the device, and ends within a piece or two, however
+ *              long the interval.
+ *   eager      0: where the iteration is not fused into the streaming kernel,
+ *              CG replays every check interval after the first, and BiCGStab
+ *              every whole piece after the first, from a HIP graph captured
  *              from the same launches (same results; fewer host launches for
  *              small lattices). 1: launch every kernel separately.
  */
@@ -124,7 +129,9 @@ typedef struct {
   int eager;
 } ufg_solve_opts;
 
-/* Solve statistics (worst case over the right-hand sides). */
+/* Solve statistics (worst case over the right-hand sides). The counts are those of
+   whole check intervals up to the one that confirmed convergence, also where the
+   last of them was left before its end; launches after it are not counted. */
 typedef struct {
   int iters[2];              /* iterations of step 1 / step 2 (CG: [0] only)  */
   long long mv;              /* applications of M or M^dagger (any precision) */

@@ -24,9 +24,11 @@ using namespace hopc;
 constexpr int kLowdThreads = 256;
 // slices per thread of the operator kernel (its loads are issued together):
 // four, two on 2D lattices of Nx <= 8, where a workgroup then still covers 8
-// or more slices (measured on 8^2 x 8000, 16 rhs: complex128 apply_M 72.6 ->
-// 59.8 us, apply_Mdag 54.6 -> 49.8 us, complex64 within 4 %; two on 2D
-// Nx = 16 was 6-14 % slower). A function of the shape alone, so that the
+// or more slices. Measured with M and M^T on lattices that run them in lowd_line.hip
+// (Nx of 8 and more reaches this kernel with a shift beyond 2 GiB per rhs only): 8^2 x
+// 8000, 16 rhs complex128 M 72.6 -> 59.8 us, M^T 54.6 -> 49.8 us, complex64 within 4 %;
+// two on 2D Nx = 16 was 6-14 % slower. The basis changes there and 2D Nx = 6 keep the
+// same shapes. A function of the shape alone, so that the
 // reduction's partial-sum count (lowd_blocks_per_rhs) follows it.
 constexpr int lowd_slices(int nx, int d) { return (d == 2 && nx <= 8) ? 2 : 4; }
 
@@ -111,9 +113,9 @@ __global__ void __launch_bounds__(kLowdThreads) hop_lowd_kernel(HopArgs<R> a, in
     const int t = (tg * KS + k) * SPW + sub;
     postv[k] = (active && t < ntau && a.post) ? a.post[(long long)t * V + l] : R(1);
   }
-  // so is the identity term, except for complex64 in dimension 1 (measured:
-  // 4-13 % faster elsewhere, apply_Mdag complex128 1D 123 -> 107 us; 1D
-  // complex64 apply_M 68 -> 72 us)
+  // so is the identity term, except for complex64 in dimension 1 (measured on 16 x 16000, 64
+  // rhs, which runs in lowd_line.hip: complex128 M^T 123 -> 107 us, 4-13 % faster elsewhere;
+  // complex64 M 68 -> 72 us)
   constexpr bool kEarlyId = !(D == 1 && sizeof(R) == 4);
   C2<R> idv[kEarlyId ? KS : 1];
   if constexpr (kEarlyId) {

@@ -244,7 +244,8 @@ __global__ void __launch_bounds__(NX * NX)
 }
 
 // The recurrence from the slab's carry and U^3: y = alpha U^3 u (+ beta u0).
-template <typename R, int NX, bool AUX>
+// Without CARRY the modes are u already (order 0 with one slice a slab).
+template <typename R, int NX, bool AUX, bool CARRY>
 __global__ void __launch_bounds__(NX * NX, sizeof(R) == 8 && NX == 16 ? 2 : 1)
     wce_last_kernel(WceArgs<R> a, CoefPtr<R, NX> cb, int ntau, int nslab) {
   constexpr int P = NX * NX, V = NX * NX * NX;
@@ -258,10 +259,8 @@ __global__ void __launch_bounds__(NX * NX, sizeof(R) == 8 && NX == 16 ? 2 : 1)
   constexpr int RS = sizeof(R), ES = sizeof(C2<R>);
   const int vo = threadIdx.x * RS;
   const auto rl = make_rsrc(a.lam, V * RS);
-  C2<R> U[NX];
-#pragma unroll
-  for (int z = 0; z < NX; ++z) U[z] = zero_of<C2<R>>();
-  if (a.carry) {
+  C2<R> U[CARRY ? NX : 1];
+  if constexpr (CARRY) {
     const auto rc = make_rsrc(a.carry + ((long long)r * nslab + sb) * 2 * V, 2 * V * RS);
 #pragma unroll
     for (int z = 0; z < NX; ++z)
@@ -290,12 +289,14 @@ __global__ void __launch_bounds__(NX * NX, sizeof(R) == 8 && NX == 16 ? 2 : 1)
     } else {
       load(k, X);
     }
+    if constexpr (CARRY) {
 #pragma unroll
-    for (int z = 0; z < NX; ++z) {
-      const R lam = bload_real<R>(rl, vo, z * P * RS);
-      const C2<R> d = C2<R>{lam * U[z].x, lam * U[z].y};
-      U[z] = C2<R>{X[z].x + d.x, X[z].y + d.y};
-      X[z] = a.subtract ? d : U[z];
+      for (int z = 0; z < NX; ++z) {
+        const R lam = bload_real<R>(rl, vo, z * P * RS);
+        const C2<R> d = C2<R>{lam * U[z].x, lam * U[z].y};
+        U[z] = C2<R>{X[z].x + d.x, X[z].y + d.y};
+        X[z] = a.subtract ? d : U[z];
+      }
     }
     slice_T3<R, NX, 2>(cb, lds, l, X);
     C2<R> A[AUX ? NX : 1];
@@ -337,10 +338,10 @@ __device__ __forceinline__ double ipow(double x, int n) {
 // a column per (grid.y, lane), no division, buffer loads whose range check does
 // for the ends of a chunk (a launch at 12^3 x 200: 6.5 us with 64-bit column
 // numbers and addresses, 32 chunks and a loop over their sums; 4.0 us so).
-template <typename R, int MODES, int CHUNKS, int KEEP>
+template <typename R, int MODES, int CHUNKS, int KEEP, bool INCLUSIVE>
 __global__ void __launch_bounds__(MODES* CHUNKS)
     wce_scan_kernel(R* carry, const double* __restrict__ lam_mode, int V, int ntau, int slab,
-                    int nslab, int adjoint, int inclusive, const int* gate) {
+                    int nslab, int adjoint, const int* gate) {
   __shared__ double cend[CHUNKS][MODES];
   __shared__ double cpow[CHUNKS][MODES];
   constexpr int RS = sizeof(R);
@@ -397,47 +398,47 @@ __global__ void __launch_bounds__(MODES* CHUNKS)
 #pragma unroll
   for (int i = 0; i < KEEP; ++i) {
     const double p = k0 + i == short_k ? lamL : lamS, u = double(G[i]) + p * v;
-    bstore_real<R>(R(inclusive ? u : v), rc, at(k0 + i), 0);
+    bstore_real<R>(R(INCLUSIVE ? u : v), rc, at(k0 + i), 0);
     v = u;
   }
 #pragma unroll 4
   for (int k = k0 + KEEP; k < k1; ++k) {
     const R g = bload_real<R>(rc, at(k), 0);
     const double p = k == short_k ? lamL : lamS, u = double(g) + p * v;
-    bstore_real<R>(R(inclusive ? u : v), rc, at(k), 0);
+    bstore_real<R>(R(INCLUSIVE ? u : v), rc, at(k), 0);
     v = u;
   }
 }
 
-template <typename R, int MODES, int CHUNKS, int KEEP>
+template <typename R, int MODES, int CHUNKS, int KEEP, bool INCLUSIVE>
 int launch_scan_shape(const Lattice& L, R* carry, int slab, int nslab, int nrhs, bool adjoint,
-                      bool inclusive, const int* gate) {
+                      const int* gate) {
   constexpr int kMost = 32767;  // right-hand sides a launch: grid.y ends at 65535
   for (int r0 = 0; r0 < nrhs; r0 += kMost) {
-    hipLaunchKernelGGL((wce_scan_kernel<R, MODES, CHUNKS, KEEP>),
+    hipLaunchKernelGGL((wce_scan_kernel<R, MODES, CHUNKS, KEEP, INCLUSIVE>),
                        dim3((unsigned)((L.V + MODES - 1) / MODES),
                             (unsigned)(2 * std::min(kMost, nrhs - r0))),
                        dim3(MODES * CHUNKS), 0, L.stream, carry + (long long)r0 * nslab * 2 * L.V,
                        L.f64.lam, L.V, L.ntau, slab, nslab, adjoint ? 1 : 0,
-                       inclusive ? 1 : 0, gate ? gate + r0 : nullptr);
+                       gate ? gate + r0 : nullptr);
     UFG_HIP(hipGetLastError());
   }
   return UFG_OK;
 }
 
-template <typename R>
+template <bool INCLUSIVE, typename R>
 int launch_scan(const Lattice& L, R* carry, int slab, int nslab, int nrhs, bool adjoint,
-                bool inclusive, const int* gate) {
+                const int* gate) {
   // Many columns: wide rows, short chunks. Few: 16 modes a row to have more
   // workgroups, and chunks that fit the registers. Order-2 application, us, with
   // 32 x 8 keeping 8 / 16 x 8 keeping 16 / 16 x 16 keeping 16: 16^3 x 400, 8 rhs (80
   // slabs) complex64 274 / 293 / 285 (32 x 16); 8^3 x 160, 4 rhs (80 slabs) 42.0 / 39.8 /
   // 41.3; 6^3 x 50 (50) 20.9 / 21.1 / 23.4; 12^3 x 200 (200) 65.5 / 58.6 / 53.0.
   if (2ll * L.V * nrhs >= 64 * 256)
-    return launch_scan_shape<R, 32, 8, 8>(L, carry, slab, nslab, nrhs, adjoint, inclusive, gate);
+    return launch_scan_shape<R, 32, 8, 8, INCLUSIVE>(L, carry, slab, nslab, nrhs, adjoint, gate);
   if (nslab <= 128)
-    return launch_scan_shape<R, 16, 8, 16>(L, carry, slab, nslab, nrhs, adjoint, inclusive, gate);
-  return launch_scan_shape<R, 16, 16, 16>(L, carry, slab, nslab, nrhs, adjoint, inclusive, gate);
+    return launch_scan_shape<R, 16, 8, 16, INCLUSIVE>(L, carry, slab, nslab, nrhs, adjoint, gate);
+  return launch_scan_shape<R, 16, 16, 16, INCLUSIVE>(L, carry, slab, nslab, nrhs, adjoint, gate);
 }
 
 // The blocks of U^T and U, adjacent on the device.
@@ -484,10 +485,17 @@ int launch_pair(const Lattice& L, const WceArgs<R>& a, int nslab) {
   WCE_LAUNCH((wce_pair_kernel<R, NX, EPI>), sizeof(R), nslab * a.nrhs * 2, a,
              (coef_bwd<R, NX>(L)), (coef_fwd<R, NX>(L)));
 }
+template <typename R, int NX, bool AUX, bool CARRY>
+int launch_last_kernel(const Lattice& L, const WceArgs<R>& a, int nslab) {
+  WCE_LAUNCH((wce_last_kernel<R, NX, AUX, CARRY>), sizeof(C2<R>), nslab * a.nrhs, a,
+             (coef_bwd<R, NX>(L)));
+}
 template <typename R, int NX, bool AUX>
 int launch_last(const Lattice& L, const WceArgs<R>& a, int nslab) {
-  WCE_LAUNCH((wce_last_kernel<R, NX, AUX>), sizeof(C2<R>), nslab * a.nrhs, a,
-             (coef_bwd<R, NX>(L)));
+  if constexpr (NX == 16 && !AUX) {  // see wce_direct
+    if (!a.carry) return launch_last_kernel<R, NX, AUX, false>(L, a, nslab);
+  }
+  return launch_last_kernel<R, NX, AUX, true>(L, a, nslab);
 }
 #undef WCE_LAUNCH
 
@@ -605,7 +613,8 @@ int wce_modes_apply(Lattice& L, const PcPlan& pc, bool adjoint, const C2<R>* x, 
   const int nslab = (L.ntau + a.slab - 1) / a.slab;
   auto scan = [&]() -> int {
     cnt->m0inv += 1;
-    return launch_scan<R>(L, direct ? a.modes : a.carry, a.slab, nslab, nrhs, adjoint, direct, gate);
+    if (direct) return launch_scan<true>(L, a.modes, a.slab, nslab, nrhs, adjoint, gate);
+    return launch_scan<false>(L, a.carry, a.slab, nslab, nrhs, adjoint, gate);
   };
   a.src = x;
   if (src) {

@@ -323,18 +323,25 @@ __device__ __forceinline__ double wsum(double v) {
 // TR = 1: the transform's y and x stages on MFMA (complex64, Nx = 16, plain
 // operator only; see slice_T3_mfma16); TR = 2: every stage through 16-point
 // DFTs (same restriction; see slice_T3_fft16).
-// At most three waves per SIMD for the complex64 Nx = 16 M^T with scaling and
-// auxiliary term: aiming at the four that its LDS slice allows, the compiler
-// spills (123 VGPRs and scratch; a degree-8 Chebyshev application on 16^3 x 217,
-// 5 rhs 347 -> 367 us).
-template <typename R, int NX, int DIR, bool GENERAL>
+// Waves per SIMD the compiler may aim at.
+// Three for the complex64 Nx = 16 M^T with scaling and auxiliary term: aiming at the
+// four that its LDS slice allows, the compiler spills (123 VGPRs and scratch; a degree-8
+// Chebyshev application on 16^3 x 217, 5 rhs 347 -> 367 us).
+// Two for the complex128 Nx = 16 operators that form their source while loading: the 68 KB
+// slice admits two workgroups a CU, and registers saved for a third wave only put the
+// loads of a slice one behind the other. t = A s on 16^3 x 400, 8 rhs, M / M^T: 146 and 166
+// VGPRs 206.5 / 204.4 us, 182 and 185 VGPRs 195.6 / 192.6, the FP64 solve 2.697 ->
+// 2.642 s; an iteration on 16^3 x 64, 1 rhs 45.3 / 48.3 -> 42.4 / 45.1 us. The plain source
+// has no such gain (v = A p 124.4 / 122.3 -> 125.7 / 122.9).
+template <typename R, int NX, int DIR, bool GENERAL, int SRC>
 constexpr int hop_max_waves() {
+  if (NX == 16 && sizeof(R) == 8 && SRC != 0) return 2;
   return sizeof(R) == 4 && NX == 16 && DIR > 0 && GENERAL ? 3 : 8;
 }
 
 template <typename R, int NX, int DIR, bool GENERAL, int SRC, int RED, int TR = 0>
 __global__ void __launch_bounds__(NX * NX)
-    __attribute__((amdgpu_waves_per_eu(1, hop_max_waves<R, NX, DIR, GENERAL>())))
+    __attribute__((amdgpu_waves_per_eu(1, hop_max_waves<R, NX, DIR, GENERAL, SRC>())))
     hop_stream_kernel(HopArgs<R> a, SplitCoef<R, NX> c, int ntau, int nslab, int xg, int ri) {
   static_assert(TR == 0 || (sizeof(R) == 4 && NX == 16 && SRC == 0 && RED == 0 && !GENERAL),
                 "the MFMA and DFT transform routes exist for the plain complex64 Nx = 16 "
